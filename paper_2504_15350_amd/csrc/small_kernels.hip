@@ -632,32 +632,156 @@ __device__ __forceinline__ double shfl_xor_d(double v, int mask) {
     return __shfl_xor(v, mask, 64);
 }
 
-// Value of lane (l ^ pattern) within rows of 16 by a DPP move (both halves).
+// Value of another lane of the row of 16 by a DPP move (both halves); every lane has a source, so
+// nothing is kept of the destination (bound_ctrl).
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double v) {
     const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, true);
     return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
-constexpr int DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_QUAD_1032 = 0xB1, DPP_QUAD_2301 = 0x4E;
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
+}
+constexpr int DPP_XOR1 = 0xB1 /* quad_perm 1,0,3,2 */, DPP_XOR2 = 0x4E /* quad_perm 2,3,0,1 */,
+              DPP_XOR7 = 0x141 /* row_half_mirror */, DPP_XOR15 = 0x140 /* row_mirror */,
+              DPP_XOR8 = 0x128 /* row_ror:8 */;
 
-// Sum over each aligned group of 8 lanes, the same bits in all 8 lanes
-// (the three steps pair commuting operands).
-__device__ __forceinline__ double sum8(double x) {
-    x += dpp_d<DPP_HALF_MIRROR>(x);
-    x += dpp_d<DPP_QUAD_1032>(x);
-    x += dpp_d<DPP_QUAD_2301>(x);
-    return x;
+// x of lanes l and l ^ 16 (permlane16_swap) or l ^ 32 (permlane32_swap), in the same order in both:
+// a swap of a register with its copy leaves the even rows' (lower half's) values in both places of
+// the first result and the odd rows' (upper half's) in both places of the second.
+template <int BIT>
+__device__ __forceinline__ void both_of(unsigned v, unsigned& even, unsigned& odd) {
+    const auto r = BIT == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)
+                             : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    even = r[0];
+    odd = r[1];
+}
+template <int BIT>
+__device__ __forceinline__ double pair_sum(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    unsigned l0, l1, h0, h1;
+    both_of<BIT>((unsigned)b, l0, l1);
+    both_of<BIT>((unsigned)(b >> 32), h0, h1);
+    return __builtin_bit_cast(double, ((unsigned long long)h0 << 32) | l0) +
+           __builtin_bit_cast(double, ((unsigned long long)h1 << 32) | l1);
+}
+// Sum over the eight lanes that share l mod 8, the same bits in all of them (commuting operands).
+__device__ __forceinline__ double sum_sub(double x) {
+    x += dpp_d<DPP_XOR8>(x);
+    return pair_sum<32>(pair_sum<16>(x));
+}
+// Maximum over the wave of non-NaN values, in every lane.
+__device__ __forceinline__ double wave_max(double x) {
+    x = fmax(x, dpp_d<DPP_XOR1>(x));
+    x = fmax(x, dpp_d<DPP_XOR2>(x));
+    x = fmax(x, dpp_d<DPP_XOR7>(x));
+    x = fmax(x, dpp_d<DPP_XOR15>(x));
+    return fmax(fmax(read_lane(x, 0), read_lane(x, 16)), fmax(read_lane(x, 32), read_lane(x, 48)));
+}
+__device__ __forceinline__ int wave_max(int x) {
+    x = max(x, dpp_i<DPP_XOR1>(x));
+    x = max(x, dpp_i<DPP_XOR2>(x));
+    x = max(x, dpp_i<DPP_XOR7>(x));
+    x = max(x, dpp_i<DPP_XOR15>(x));
+    unsigned a, b;
+    both_of<16>((unsigned)x, a, b);
+    x = max((int)a, (int)b);
+    both_of<32>((unsigned)x, a, b);
+    return max((int)a, (int)b);
 }
 
-// Maximum over the wave, returned uniformly.
-__device__ __forceinline__ double wave_max(double x) {
-    x = fmax(x, dpp_d<DPP_HALF_MIRROR>(x));
-    x = fmax(x, dpp_d<DPP_QUAD_1032>(x));
-    x = fmax(x, dpp_d<DPP_QUAD_2301>(x));
-    x = fmax(x, dpp_d<DPP_MIRROR>(x));
-    return fmax(fmax(read_lane(x, 0), read_lane(x, 16)), fmax(read_lane(x, 32), read_lane(x, 48)));
+// a[k] += x(lane 16 (l / 16) + k) m for k < 16: the multipliers of a row of 16 lanes, each broadcast
+// over its row by the multiply-add itself (no LDS broadcast reads, no register moves). The wait
+// states a DPP operand needs after a VALU write are inside.
+__device__ __forceinline__ void fma16_bcast(double (&a)[16], double x, double m) {
+    asm volatile(
+        "s_nop 1\n"
+        "v_fmac_f64_dpp %0, %8, %9 row_newbcast:0 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %8, %9 row_newbcast:1 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %2, %8, %9 row_newbcast:2 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %3, %8, %9 row_newbcast:3 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %4, %8, %9 row_newbcast:4 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %5, %8, %9 row_newbcast:5 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %6, %8, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %7, %8, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n"
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7])
+        : "v"(x), "v"(m));
+    asm volatile(
+        "s_nop 1\n"
+        "v_fmac_f64_dpp %0, %8, %9 row_newbcast:8 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %8, %9 row_newbcast:9 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %2, %8, %9 row_newbcast:10 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %3, %8, %9 row_newbcast:11 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %4, %8, %9 row_newbcast:12 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %5, %8, %9 row_newbcast:13 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %6, %8, %9 row_newbcast:14 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %7, %8, %9 row_newbcast:15 row_mask:0xf bank_mask:0xf\n"
+        : "+v"(a[8]), "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15])
+        : "v"(x), "v"(m));
+}
+
+// One rotation per group of eight lanes that makes the columns own and part (RPL rows per lane)
+// orthogonal: own' = c own - s part, part' = s own + c part; no, np are their squared norms. The
+// half-angle tangent u comes from the hardware estimates (2^-23: that fraction of the inner product
+// removed is left over); c = (1 - u^2) / (1 + u^2) and s = 2 u / (1 + u^2) follow from u to FP64, so
+// the rotation is orthogonal to rounding whatever the error of u.
+// SYM: the two groups of a pair within a block compute the same rotation, each as "own"; every
+// expression is then symmetric (or antisymmetric) in the exchange bit for bit, `low` deciding where
+// the norms are equal. Otherwise the update is three shears in place, (1 -u; 0 1) (1 0; s 1) (1 -u; 0 1).
+template <int RPL, bool SYM>
+__device__ __forceinline__ bool jacobi_rotate(double (&own)[RPL], double (&part)[RPL], double& no, double& np,
+                                              double tol2, bool low) {
+    double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+    for (int k = 0; k < RPL; k += 2) {
+        g0 = fma(own[k], part[k], g0);
+        g1 = fma(own[k + 1], part[k + 1], g1);
+    }
+    const double ga = sum_sub(g0 + g1);
+    const bool rot = ga * ga > tol2 * (no * np);  // |ga| > tol sqrt(no np); false when a column is zero
+    if (__ballot(rot) == 0) return false;
+    // tan(theta) = y / p, tan(theta / 2) = y / (p + sqrt(2 r p)), with y = |2 ga|, r = sqrt(d^2 + y^2),
+    // p = r + |d|, d = np - no; theta has the sign of d ga
+    double d = np - no;
+    const double e2 = ga + ga;
+    if (SYM && d == 0.0) d = low ? 0.0 : -0.0;
+    const double h2 = fma(d, d, e2 * e2);
+    const double r = h2 * __builtin_amdgcn_rsq(h2);
+    const double p = r + fabs(d);
+    const double w = (r + r) * p;
+    double u = fabs(e2) * __builtin_amdgcn_rcp(fma(w, __builtin_amdgcn_rsq(w), p));
+    double t = fabs(e2) * __builtin_amdgcn_rcp(p);
+    const double sgn = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, d) ^
+                                                      __builtin_bit_cast(unsigned long long, e2));
+    u = rot ? __builtin_copysign(u, sgn) : 0.0;
+    t = rot ? __builtin_copysign(t, sgn) : 0.0;
+    const double q = fma(u, u, 1.0);
+    double y = __builtin_amdgcn_rcp(q);
+    const double e = fma(-q, y, 1.0);
+    y = fma(y, fma(e, e, e), y);  // 1 / q: the estimate's error cubed
+    const double s = (u + u) * y;
+    if constexpr (SYM) {
+        const double c = fma(-u, u, 1.0) * y;
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) {
+            const double a = own[k], b = part[k];
+            own[k] = fma(-s, b, c * a);
+            part[k] = fma(s, a, c * b);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) own[k] = fma(-u, part[k], own[k]);
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) part[k] = fma(s, own[k], part[k]);
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) own[k] = fma(-u, part[k], own[k]);
+    }
+    no = fma(-t, ga, no);
+    np = fma(t, ga, np);
+    return rot;
 }
 
 // Preconditioned one-sided Jacobi (Drmac and Veselic, SIMAX 2008): with the
@@ -669,267 +793,269 @@ __device__ __forceinline__ double wave_max(double x) {
 // descending sigma_k = ||(P L V)[:, k]||; factorisation stops at the first
 // pivot below lp u times the largest diagonal entry of G (the remaining
 // columns are zero, as are their sigma and UB columns).
-// lp <= 64: the factorisation runs in one wave without moving data: lane i
-// keeps row i of the Schur complement (original order) in registers, the
-// pivot is the largest remaining diagonal entry (lowest index on ties), its
-// row is published through LDS, and column j of P L is stored in original
-// row order. lp > 64: the workgroup factorises with symmetric swaps in LDS.
-// Sweeps: round-robin pairs, eight lanes per pair (each lane two pairs of
-// adjacent rows per 16-row group, 16-byte LDS accesses), sums by DPP.
+// Factorisation: lane i of wave w keeps rows i, i + 64 and columns 16 w .. 16 w + 15 of the
+// Schur complement (original order) in registers. Every wave carries the diagonal and finds the
+// pivot by itself (the largest remaining entry as an FP32 fraction of the largest, lowest index
+// on ties; the next pivot is found while the update runs), the lane holding the pivot row publishes
+// its part, and one barrier later every wave reads the row as the multipliers (the matrix is
+// symmetric): one barrier per step, no data moved, and the reciprocal root is taken before it.
+// Sweeps: the columns form blocks of eight. A wave holds two blocks in registers, one column of
+// each per group of eight lanes (group = lane mod 8, rows 16 kc + 2 (lane / 8), + 1), so the 8 x 8
+// pairs between them, and the pairs within each once per sweep, need no LDS and no barrier: from
+// one round to the next the second block's columns move between the groups by one DPP lane
+// exchange. Blocks meet by the circle method: lp / 8 - 1 exchanges through LDS, one barrier each,
+// per sweep of lp - 1 rounds. A round is bound by the issue of one wave's instructions (about 8
+// cycles each with one wave per SIMD, 6 with two): 760 cycles at lp = 64, 1650 at lp = 128, where
+// a round through LDS with its own barrier took 1500 and 3300. Per launch, spectra decaying by
+// e^-6 over l: lp = 32, 64, 96, 128 59, 176, 459, 781 us (86, 275, 776, 1390 us before); the
+// factorisation is 28 us of it at lp = 64 and 95 us at lp = 128. Sixteen lanes per pair, and so two
+// waves per SIMD at lp = 64, would issue 1.6 x the instructions for 1.3 x the issue rate.
+// LDS holds the blocks as register images: chunk kc of block b at ((b KC + kc) 64 + lane) 16 bytes,
+// so every access is 1 KB contiguous.
+// Squared norms are recomputed at every load and updated over the eight rounds after it; a sweep
+// without rotations therefore tests every pair with norms just computed.
 // Factor route (C non-NULL): the columns of C (C C^T = T T^T, from an
 // orthonormal basis of T^T rather than from the Gram matrix) are loaded as
 // they are, with no permutation, and the sweeps start at once.
-template <int LP, int NTHR>
+template <int LP>
 __device__ __forceinline__ void jacobi_chol_body(const double* __restrict__ G, int l, double* __restrict__ UB,
-                                                 double* __restrict__ sig, int* flags, double tol, int* sweeps_out,
-                                                 const double* __restrict__ C = nullptr, int64_t ldc = 0) {
-    constexpr int NPAIR = LP / 2;
-    constexpr int TPP = NTHR / NPAIR;
-    constexpr int RPT = LP / TPP;
-    static_assert(TPP == 8 && RPT * TPP == LP, "pair layout: eight lanes per pair");
-    // column stride: the smallest >= LP that is 16 mod 64 doubles, so consecutive columns start
-    // 128 bytes apart within the LDS's 512-byte window. The 32 lanes of one cycle are four column
-    // pairs' 128-byte runs (eight lanes per pair), mostly of consecutive columns: with LP + 2 they
-    // overlapped and 41 % of the LDS cycles were bank conflicts
-    constexpr int LDW = LP + (((16 - LP) % 64) + 64) % 64;
-    __shared__ __attribute__((aligned(16))) double W[LP * LDW];   // A[row][col] at W[col * LDW + row]
+                                                 double* __restrict__ sig, int* flags, double tol,
+                                                 const double* __restrict__ C, int64_t ldc) {
+    constexpr int NW = LP / 16, NTHR = 64 * NW, NB = 2 * NW, KC = LP / 16, RPL = 2 * KC, CPL = (LP + 63) / 64;
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(16))) double W[LP * LP];         // register images of the blocks
+    __shared__ __attribute__((aligned(16))) double buf[2][64 * CPL];   // pivot rows, alternating
     __shared__ double nrm[LP];
-    __shared__ int perm[LP];
-    __shared__ int s_rank, s_rot;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // place of row `row` of column `col` in W
+    auto at = [](int row, int col) {
+        return (((col >> 3) * KC + (row >> 4)) * 64 + ((row & 15) >> 1) * 8 + (col & 7)) * 2 + (row & 1);
+    };
     if (C != nullptr) {
-        for (int e = tid; e < LP * LDW; e += NTHR) {
-            const int c = e / LDW, row = e % LDW;
-            W[e] = (c < l && row < l) ? C[(int64_t)c * ldc + row] : 0.0;
+        const GLOBAL double* Cg = gbl(C);
+        for (int e = tid; e < LP * LP; e += NTHR) {
+            const int c = e / LP, row = e % LP;
+            W[at(row, c)] = (c < l && row < l) ? Cg[(int64_t)c * ldc + row] : 0.0;
         }
-        for (int c = tid; c < LP; c += NTHR) perm[c] = c;
-        __syncthreads();
-    } else if constexpr (LP <= 64) {
-        __shared__ __attribute__((aligned(16))) double rowbuf[64];
-        for (int e = tid; e < LP * LDW; e += NTHR) W[e] = 0.0;
-        for (int c = tid; c < LP; c += NTHR) perm[c] = c;
-        __syncthreads();
-        if (wave == 0) {
-            const int i = lane;
-            const bool live = i < l;
-            double a[LP];  // row i of the Schur complement, original column order
-#pragma unroll
-            for (int k = 0; k < LP; ++k) a[k] = (live && k < l) ? G[i * LP + k] : 0.0;
-            double dg = live ? G[i * LP + i] : 0.0;
-            const double thr = (double)LP * 0x1.0p-53 * wave_max(live ? dg : 0.0);
-            bool done = !live;
-            int rank = l;
-            for (int j = 0; j < l; ++j) {
-                const double v = done ? -1.0 : dg;
-                const double vmax = wave_max(v);
-                if (!(vmax > thr)) {  // remaining Schur complement negligible (or not finite)
-                    rank = j;
-                    break;
-                }
-                const int pv = __ffsll((unsigned long long)__ballot(!done && v == vmax)) - 1;
-                if (i == pv) {
-#pragma unroll
-                    for (int k = 0; k < LP; ++k) rowbuf[k] = a[k];
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                const double app = rowbuf[pv];
-                const double inv = rsqrt_nr(app), ljj = app * inv;
-                double lij = done ? 0.0 : rowbuf[i] * inv;
-                if (i == pv) {
-                    lij = ljj;
-                    done = true;
-                }
-                if (i < LP) W[j * LDW + i] = lij;
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                if (!done) {
-#pragma unroll
-                    for (int k = 0; k < LP; ++k) a[k] -= lij * W[j * LDW + k];
-                    dg -= lij * lij;
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            }
-            if (lane == 0) s_rank = rank;
-        }
-        __syncthreads();
-        if (tid == 0 && s_rank < l) atomicOr(flags, DEV_FLAG_RANK_CUT);
     } else {
-        __shared__ double s_val[NTHR / 64];
-        __shared__ int s_idx[NTHR / 64];
-        __shared__ int s_piv;
-        __shared__ double s_dmax;
-        for (int e = tid; e < LP * LP; e += NTHR) {
-            const int c = e / LP, row = e % LP;
-            W[c * LDW + row] = (c < l && row < l) ? G[row * LP + c] : 0.0;
+        const GLOBAL double* Gg = gbl(G);
+        for (int e = tid; e < LP * LP; e += NTHR) W[e] = 0.0;
+        double a[CPL][16], dg[CPL];
+        bool done[CPL];
+#pragma unroll
+        for (int cc = 0; cc < CPL; ++cc) {
+            const int row = lane + 64 * cc;
+            const bool live = row < l;
+            const int rc = row < LP ? row : 0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                a[cc][k] = Gg[(16 * wave + k) * LP + rc];
+            }
+            dg[cc] = Gg[rc * LP + rc];
+            done[cc] = !live;
         }
-        for (int c = tid; c < LP; c += NTHR) perm[c] = c;
-        if (tid == 0) {
-            double dm = 0.0;
-            for (int i = 0; i < l; ++i) dm = fmax(dm, G[i * LP + i]);
-            s_dmax = dm;
-            s_rank = l;
+        // rows and columns past l (read all the same, so that the loads are in flight together) count as zero
+#pragma unroll
+        for (int cc = 0; cc < CPL; ++cc) {
+            const bool live = lane + 64 * cc < l;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                asm volatile("" : "+v"(a[cc][k]));
+                a[cc][k] = (live && 16 * wave + k < l) ? a[cc][k] : 0.0;
+            }
+            asm volatile("" : "+v"(dg[cc]));
+            dg[cc] = live ? dg[cc] : 0.0;
         }
+        // the largest diagonal entry, as the scale of the FP32 pivot search
+        double dm = dg[0];
+        if constexpr (CPL > 1) dm = fmax(dm, dg[CPL - 1]);
+        dm = wave_max(dm);
+        const double scale = dm > 0.0 ? 1.0 / dm : 0.0;
+        const int thr = __builtin_bit_cast(int, (float)LP * 0x1.0p-53f);
+        // the next pivot: row, and whether one is left that is not negligible (or not finite).
+        // The FP32 fractions are compared by their bits (non-negative, so the orders agree; a
+        // negative or NaN remainder and a finished row lose against thr).
+        auto find = [&](int& pv) {
+            int v[CPL], vm = -1;
+#pragma unroll
+            for (int cc = 0; cc < CPL; ++cc) {
+                const double x = dg[cc] * scale;
+                v[cc] = (!done[cc] && x <= 2.0) ? __builtin_bit_cast(int, (float)x) : -1;
+                vm = max(vm, v[cc]);
+            }
+            const int vmax = wave_max(vm);
+            pv = 0;
+#pragma unroll
+            for (int cc = CPL - 1; cc >= 0; --cc) {
+                const unsigned long long m = __ballot(v[cc] == vmax);
+                if (m != 0) pv = 64 * cc + __ffsll(m) - 1;
+            }
+            return __builtin_amdgcn_readfirstlane(vmax) > thr;
+        };
+        int rank = l, pv;
+        bool more = find(pv);
         __syncthreads();
-        const double thr = (double)LP * 0x1.0p-53 * s_dmax;
-        // diagonally pivoted Cholesky (right-looking, full symmetric storage)
         for (int j = 0; j < l; ++j) {
-            // pivot: largest remaining diagonal entry, lowest index on ties
-            double bv = -1.0;
-            int bi = LP;
-            for (int i = j + tid; i < l; i += NTHR) {
-                const double v = W[i * LDW + i];
-                if (v > bv) { bv = v; bi = i; }
+            if (!more) {  // the same in every wave
+                rank = j;
+                break;
             }
-            for (int off = 32; off > 0; off >>= 1) {
-                const double ov = shfl_xor_d(bv, off);
-                const int oi = __shfl_xor(bi, off, 64);
-                if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-            }
-            if (lane == 0) { s_val[wave] = bv; s_idx[wave] = bi; }
-            __syncthreads();
-            if (tid == 0) {
-                double v = s_val[0];
-                int ix = s_idx[0];
-                for (int w = 1; w < NTHR / 64; ++w)
-                    if (s_val[w] > v || (s_val[w] == v && s_idx[w] < ix)) { v = s_val[w]; ix = s_idx[w]; }
-                s_piv = ix;
-                if (!(v > thr)) s_rank = j;
-            }
-            __syncthreads();
-            if (s_rank == j) break;
-            const int pv = s_piv;
-            if (pv != j) {  // symmetric swap of rows and columns j and pv
-                for (int k = tid; k < LP; k += NTHR) {
-                    const double a = W[k * LDW + j];
-                    W[k * LDW + j] = W[k * LDW + pv];
-                    W[k * LDW + pv] = a;
+            double* pr = buf[j & 1];
+            const int pl = pv & 63;
+            const double app = CPL > 1 && pv >= 64 ? read_lane(dg[CPL - 1], pl) : read_lane(dg[0], pl);
+#pragma unroll
+            for (int cc = 0; cc < CPL; ++cc)
+                if (lane + 64 * cc == pv) {
+#pragma unroll
+                    for (int k = 0; k < 16; k += 2)
+                        *reinterpret_cast<d2*>(pr + 16 * wave + k) = d2{a[cc][k], a[cc][k + 1]};
                 }
-                __syncthreads();
-                for (int k = tid; k < LP; k += NTHR) {
-                    const double a = W[j * LDW + k];
-                    W[j * LDW + k] = W[pv * LDW + k];
-                    W[pv * LDW + k] = a;
+            const double inv = rsqrt_nr(app), ljj = app * inv;
+            __syncthreads();
+            double lij[CPL], m[CPL];
+#pragma unroll
+            for (int cc = 0; cc < CPL; ++cc) lij[cc] = pr[lane + 64 * cc];  // rows >= LP: never used
+            const double rk = pr[16 * wave + (lane & 15)];
+#pragma unroll
+            for (int cc = 0; cc < CPL; ++cc) {
+                const int row = lane + 64 * cc;
+                lij[cc] = done[cc] ? 0.0 : lij[cc] * inv;
+                if (row == pv) {
+                    done[cc] = true;
+                    lij[cc] = ljj;
                 }
-                if (tid == 0) {
-                    const int t = perm[j];
-                    perm[j] = perm[pv];
-                    perm[pv] = t;
-                }
-                __syncthreads();
+                if (row < LP && wave == j % NW) W[at(row, j)] = lij[cc];
+                dg[cc] = fma(-lij[cc], lij[cc], dg[cc]);
+                m[cc] = -lij[cc] * inv;
             }
-            const double ljj = sqrt(W[j * LDW + j]);
-            const double inv = 1.0 / ljj;
-            __syncthreads();
-            for (int i = j + 1 + tid; i < l; i += NTHR) W[j * LDW + i] *= inv;   // column j below the diagonal
-            if (tid == 0) W[j * LDW + j] = ljj;
-            __syncthreads();
-            // trailing update, both triangles: A[i][k] -= L[i][j] L[k][j]
-            const int nt = l - j - 1;
-            for (int e = tid; e < nt * nt; e += NTHR) {
-                const int k = j + 1 + e / nt, i = j + 1 + e % nt;
-                W[k * LDW + i] -= W[j * LDW + i] * W[j * LDW + k];
-            }
-            __syncthreads();
+            more = find(pv);
+#pragma unroll
+            for (int cc = 0; cc < CPL; ++cc) fma16_bcast(a[cc], rk, m[cc]);
         }
-        // L: lower triangle of the first `rank` columns; everything else zero
-        const int rank = s_rank;
         if (tid == 0 && rank < l) atomicOr(flags, DEV_FLAG_RANK_CUT);
-        for (int e = tid; e < LP * LP; e += NTHR) {
-            const int c = e / LP, row = e % LP;
-            if (c >= rank || row < c || row >= l) W[c * LDW + row] = 0.0;
-        }
-        __syncthreads();
     }
     // ---- one-sided Jacobi on the columns ----
-    const int pr = tid / TPP, sub = tid % TPP;
+    const int grp = lane & 7, sub = lane >> 3;
+    const double tol2 = tol * tol;
+    double A[RPL], B[RPL];
+    auto load = [&](double (&x)[RPL], int b) {
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) {
+            const d2 v = *reinterpret_cast<const d2*>(W + ((b * KC + kc) * 64 + lane) * 2);
+            x[2 * kc] = v[0];
+            x[2 * kc + 1] = v[1];
+        }
+    };
+    auto store = [&](const double (&x)[RPL], int b, int ln) {
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc)
+            *reinterpret_cast<d2*>(W + ((b * KC + kc) * 64 + ln) * 2) = d2{x[2 * kc], x[2 * kc + 1]};
+    };
+    auto norm2 = [&](const double (&x)[RPL]) {
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int k = 0; k < RPL; k += 2) {
+            s0 = fma(x[k], x[k], s0);
+            s1 = fma(x[k + 1], x[k + 1], s1);
+        }
+        return sum_sub(s0 + s1);
+    };
+    auto move = [&](auto ctrl, double (&x)[RPL], double& nx) {
+        constexpr int CTRL = decltype(ctrl)::value;
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) x[k] = dpp_d<CTRL>(x[k]);
+        nx = dpp_d<CTRL>(nx);
+    };
+    // group offsets of the eight rounds: 0, then 1, 3, 2, 5, 4, 6, 7
+    std::integral_constant<int, DPP_XOR1> x1;
+    std::integral_constant<int, DPP_XOR2> x2;
+    std::integral_constant<int, DPP_XOR7> x7;
+    // the 28 pairs within a block: each pair computed by both of its groups
+    auto within = [&](double (&x)[RPL], double& nx) {
+        double P[RPL], np = nx;
+        bool rot = false;
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) P[k] = x[k];
+        auto step = [&](auto ctrl, int k) {
+            move(ctrl, P, np);
+            rot |= jacobi_rotate<RPL, true>(x, P, nx, np, tol2, grp < (grp ^ k));
+        };
+        step(x1, 1); step(x2, 3); step(x1, 2); step(x7, 5); step(x1, 4); step(x2, 6); step(x1, 7);
+        return rot;
+    };
     int sweep = 0;
     constexpr int max_sweeps = 40;
+    __syncthreads();
     for (; sweep < max_sweeps; ++sweep) {
-        if (tid == 0) s_rot = 0;
-        __syncthreads();
-        bool rot = false;  // this lane's pair rotated during the sweep
-        for (int rnd = 0; rnd < LP - 1; ++rnd) {
-            int p, q;
-            if (pr == 0) {
-                p = LP - 1;
-                q = rnd;
-            } else {
-                p = rnd + pr;
-                if (p >= LP - 1) p -= LP - 1;
-                q = rnd - pr;
-                if (q < 0) q += LP - 1;
+        bool rot = false;  // this lane's pairs rotated during the sweep
+        int any = 0;
+        for (int t = 0; t < NB - 1; ++t) {
+            int ba = t + wave, bb = t - wave;  // circle method: block NB - 1 stays, the others turn
+            if (ba >= NB - 1) ba -= NB - 1;
+            if (bb < 0) bb += NB - 1;
+            if (wave == 0) ba = NB - 1;
+            load(A, ba);
+            load(B, bb);
+            double na = norm2(A), nb = norm2(B);
+            if (t == 0) {
+                rot |= within(A, na);
+                rot |= within(B, nb);
             }
-            if (p > q) {
-                const int t = p;
-                p = q;
-                q = t;
-            }
-            // lane sub: rows 16 k + 2 sub, 16 k + 2 sub + 1 (k < RPT / 2)
-            typedef double d2 __attribute__((ext_vector_type(2)));
-            d2 wp[RPT / 2], wq[RPT / 2];
-#pragma unroll
-            for (int k = 0; k < RPT / 2; ++k) {
-                wp[k] = *reinterpret_cast<const d2*>(W + p * LDW + 16 * k + 2 * sub);
-                wq[k] = *reinterpret_cast<const d2*>(W + q * LDW + 16 * k + 2 * sub);
-            }
-            double al = 0.0, be = 0.0, ga = 0.0;
-#pragma unroll
-            for (int k = 0; k < RPT / 2; ++k)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    al += wp[k][h] * wp[k][h];
-                    be += wq[k][h] * wq[k][h];
-                    ga += wp[k][h] * wq[k][h];
-                }
-            al = sum8(al);
-            be = sum8(be);
-            ga = sum8(ga);
-            if (al > 0.0 && be > 0.0 && ga * ga > (tol * tol) * (al * be)) {  // |ga| > tol sqrt(al be)
-                // t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), zeta = (be - al) / (2 ga), written as
-                // t = sign(zeta) |2 ga| / (|be - al| + sqrt((be - al)^2 + (2 ga)^2)); c = 1 / sqrt(1 + t^2)
-                const double d = be - al, e2 = 2.0 * ga;
-                const double sg = (d == 0.0 || ((d > 0.0) == (e2 > 0.0))) ? 1.0 : -1.0;
-                const double h2 = fma(d, d, e2 * e2);
-                const double t = sg * fabs(e2) * rcp_nr(fabs(d) + h2 * rsqrt_nr(h2));
-                const double c = rsqrt_nr(fma(t, t, 1.0)), s = c * t;
-#pragma unroll
-                for (int k = 0; k < RPT / 2; ++k) {
-                    *reinterpret_cast<d2*>(W + p * LDW + 16 * k + 2 * sub) = c * wp[k] - s * wq[k];
-                    *reinterpret_cast<d2*>(W + q * LDW + 16 * k + 2 * sub) = s * wp[k] + c * wq[k];
-                }
-                rot = true;
-            }
-            __syncthreads();
+            rot |= jacobi_rotate<RPL, false>(A, B, na, nb, tol2, true);
+            auto step = [&](auto ctrl) {
+                move(ctrl, B, nb);
+                rot |= jacobi_rotate<RPL, false>(A, B, na, nb, tol2, true);
+            };
+            step(x1); step(x2); step(x1); step(x7); step(x1); step(x2); step(x1);
+            store(A, ba, lane);
+            store(B, bb, lane ^ 7);  // the last partner was the column of group grp ^ 7
+            // a slot is written by its holder and, after the barrier, read and later written by the next
+            // holder only
+            if (t < NB - 2) __syncthreads();
+            else any = __syncthreads_or(rot);
         }
-        // one flag write per wave and sweep (a shared write every round costs 7 %)
-        if (__ballot(rot) != 0 && lane == 0) s_rot = 1;
-        __syncthreads();
-        if (s_rot == 0) break;
-        __syncthreads();
+        if (!any) break;
     }
     if (sweep == max_sweeps && tid == 0) atomicOr(flags, DEV_FLAG_JACOBI_SLOW);
-    if (sweeps_out != nullptr && tid == 0) *sweeps_out = sweep;
-    for (int c = tid; c < LP; c += NTHR) {
-        double s = 0.0;
-        for (int row = 0; row < LP; ++row) s += W[c * LDW + row] * W[c * LDW + row];
-        nrm[c] = sqrt(s);
+    load(A, 2 * wave);
+    load(B, 2 * wave + 1);
+    const double va = sqrt(norm2(A)), vb = sqrt(norm2(B));
+    const int ca = 16 * wave + grp, cb = ca + 8;
+    if (sub == 0) {
+        nrm[ca] = va;
+        nrm[cb] = vb;
     }
     __syncthreads();
-    for (int c = tid; c < LP; c += NTHR) {
-        const double v = nrm[c];
-        int rank_c = 0;
-        for (int k = 0; k < LP; ++k) rank_c += (nrm[k] > v) || (nrm[k] == v && k < c);
-        sig[rank_c] = v;
-        const double inv = v > 0.0 ? 1.0 / v : 0.0;
-        for (int row = 0; row < LP; ++row) UB[(int64_t)rank_c * LP + perm[row]] = W[c * LDW + row] * inv;
+    int ra = 0, rb = 0;  // ranks by descending norm, lowest column first on ties
+    for (int k = sub; k < LP; k += 8) {
+        const double v = nrm[k];
+        ra += (v > va) || (v == va && k < ca);
+        rb += (v > vb) || (v == vb && k < cb);
+    }
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) {
+        ra += __shfl_xor(ra, off, 64);
+        rb += __shfl_xor(rb, off, 64);
+    }
+    if (sub == 0) {
+        sig[ra] = va;
+        sig[rb] = vb;
+    }
+    const double ia = va > 0.0 ? 1.0 / va : 0.0, ib = vb > 0.0 ? 1.0 / vb : 0.0;
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) {
+        *reinterpret_cast<d2*>(UB + ra * LP + 16 * kc + 2 * sub) = d2{A[2 * kc] * ia, A[2 * kc + 1] * ia};
+        *reinterpret_cast<d2*>(UB + rb * LP + 16 * kc + 2 * sub) = d2{B[2 * kc] * ib, B[2 * kc + 1] * ib};
     }
 }
 
-// eight lanes per column pair: 4 lp threads per workgroup
+// lp / 16 waves per workgroup, two blocks of eight columns each
 template <int LP>
 __global__ __launch_bounds__(4 * LP) void k_jacobi(Group<JacobiArgs> g) {
     if (group_skipped(g)) return;
     const JacobiArgs& a = g.args[blockIdx.x];  // one workgroup per matrix
-    jacobi_chol_body<LP, 4 * LP>(a.G, a.l, a.UB, a.sig, a.flags, a.tol, nullptr, a.C, a.ldc);
+    jacobi_chol_body<LP>(a.G, a.l, a.UB, a.sig, a.flags, a.tol, a.C, a.ldc);
 }
 
 int jacobi_threads(int lp) { return 4 * lp; }
