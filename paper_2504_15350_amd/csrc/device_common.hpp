@@ -42,6 +42,41 @@ template <typename T> __device__ __forceinline__ int mfma_row(int kg, int v);
 template <> __device__ __forceinline__ int mfma_row<float>(int kg, int v) { return 4 * kg + v; }
 template <> __device__ __forceinline__ int mfma_row<double>(int kg, int v) { return kg + 4 * v; }
 
+// N consecutive rows i .. i + N - 1 of column j of a matrix with lim rows and n columns, zero outside,
+// in two steps so that the loads of an edge block are in flight together: run_load, one vector load, at
+// any element alignment (gfx950 global loads need no more than the element's), of the run moved inside
+// the matrix; run_fix, shifted into place and zero outside. No branch differs between lanes. (Behind a
+// branch per element the loads wait for each other: 3-7 us per edge step.) Streamed once: non-temporal.
+template <typename E, int N>
+__device__ __forceinline__ E __attribute__((ext_vector_type(N)))
+run_load(const GLOBAL E* S, int64_t ld, int64_t lim, int64_t n, int64_t i, int64_t j) {
+    typedef E V __attribute__((ext_vector_type(N)));
+    typedef E VU __attribute__((ext_vector_type(N), aligned(sizeof(E))));
+    const GLOBAL E* col = S + (j < n ? j : n - 1) * ld;
+    if (lim >= N)  // uniform
+        return (V)__builtin_nontemporal_load(reinterpret_cast<const GLOBAL VU*>(col + (i < lim - N ? i : lim - N)));
+    V v;
+#pragma unroll
+    for (int t = 0; t < N; ++t) v[t] = col[t < lim ? t : 0];  // fewer rows than the run: rows 0 .. lim - 1
+    return v;
+}
+template <typename E, int N>
+__device__ __forceinline__ E __attribute__((ext_vector_type(N)))
+run_fix(E __attribute__((ext_vector_type(N))) raw, int64_t lim, int64_t n, int64_t i, int64_t j) {
+    const int64_t is = lim < N ? 0 : i < lim - N ? i : lim - N;
+    const int d = (int)(i - is < N ? i - is : N);                            // rows of the run before row i
+    const int live = j < n ? (int)(lim - i < 0 ? 0 : lim - i < N ? lim - i : N) : 0;
+    E __attribute__((ext_vector_type(N))) v;
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        E x = raw[t];
+#pragma unroll
+        for (int k = 1; t + k < N; ++k) x = d == k ? raw[t + k] : x;
+        v[t] = t < live ? x : E(0);
+    }
+    return v;
+}
+
 // Status word bits (mirror the public RPOD_FLAG_* values).
 #define DEV_FLAG_SHIFTED     0x1
 #define DEV_FLAG_BREAKDOWN   0x2

@@ -406,7 +406,8 @@ struct Recorder {
               tiles([](const Item& it) { return (int)((it.L.nP + 255) / 256) * ((it.L.lp + 1) / 2); }));
         out.push_back(s);
     }
-    // generic tall x small product (internal operands)
+    // generic tall x small product (internal operands: their padding rows are zero and count as
+    // rows, so no row tile is ragged)
     void sx(int tin, int tout, int nt, bool upper, std::vector<SxArgs> args) {
         Step s{K_SX};
         s.tin = tin; s.tout = tout; s.nt = nt; s.upper = upper; s.vec = true;
@@ -484,7 +485,8 @@ struct Recorder {
         s.tin = L0().tin; s.nt = L0().nt; s.lo = s16 && lo; s.pass = s.lo ? 2 : 1;
         s.vec = true;
         for (const Item* it : C) {
-            s.vec = s.vec && (it->d.ld % (s16 ? 8 : 4) == 0);
+            // FP32: columns on 128-byte lines pick the step shape; otherwise 16-byte loads
+            s.vec = s.vec && (it->d.ld % (s16 ? 8 : f32 ? 32 : 4) == 0);
             const double sz = (double)dt_size(it->L.tin);
             s.bytes += (double)it->d.m * it->d.n * sz + (double)it->d.n * it->L.l * sz + (double)it->d.m * it->L.l * 4.0;
             s.flops += 2.0 * it->d.m * it->d.n * it->L.l;
@@ -631,7 +633,7 @@ struct Recorder {
         };
         auto apply = [&](auto src, auto dst, int k, bool cond) {
             return each([&](const Item& it) {
-                return SxArgs{src(it), it.L.mP, it.d.m, it.L.lp, Rx(it, k), it.L.lp, dst(it), it.L.mP, it.L.mP,
+                return SxArgs{src(it), it.L.mP, it.L.mP, it.L.lp, Rx(it, k), it.L.lp, dst(it), it.L.mP, it.L.mP,
                               cond ? P->flag(it, 1) : nullptr, cond ? 1 : 0, -1};
             });
         };
@@ -673,7 +675,7 @@ struct Recorder {
         };
         auto apply = [&](auto src, auto dst, int k, bool cond) {
             return each([&](const Item& it) {
-                return SxArgs{src(it), it.L.mP, it.d.m, it.L.lp, Rx(it, k), it.L.lp, dst(it), it.L.mP, it.L.mP,
+                return SxArgs{src(it), it.L.mP, it.L.mP, it.L.lp, Rx(it, k), it.L.lp, dst(it), it.L.mP, it.L.mP,
                               cond ? P->flag(it, 1) : nullptr, cond ? 1 : 0, -1};
             });
         };
@@ -725,7 +727,7 @@ struct Recorder {
         };
         auto apply = [&](int k, bool cond) {
             return each([&](const Item& it) {
-                return SxArgs{Q(it), it.L.mP, it.d.m, it.L.lp, Rx(it, k), it.L.lp, Q(it), it.L.mP, it.L.mP,
+                return SxArgs{Q(it), it.L.mP, it.L.mP, it.L.lp, Rx(it, k), it.L.lp, Q(it), it.L.mP, it.L.mP,
                               cond ? P->flag(it, 1) : nullptr, cond ? 1 : 0, -1};
             });
         };
@@ -778,7 +780,7 @@ struct Recorder {
     // Zw = Zt R^-1 (R from the last tall orthonormalisation): Zw = S^T Q
     void small_from_slabs() {
         sx(DT_F64, DT_F64, L0().nt, true, each([&](const Item& it) {
-               return SxArgs{P->at<char>(it, it.L.o_Zt), it.L.nP, it.d.n, it.L.lp, P->at<char>(it, it.L.o_R64[1]),
+               return SxArgs{P->at<char>(it, it.L.o_Zt), it.L.nP, it.L.nP, it.L.lp, P->at<char>(it, it.L.o_R64[1]),
                              it.L.lp, P->at<char>(it, it.L.o_Zw), it.L.nP, it.L.nP, nullptr, 0, -1};
            }));
     }
@@ -796,7 +798,7 @@ struct Recorder {
         };
         auto app = [&](size_t Layout::*src, size_t Layout::*dst, int k, bool cond) {
             return each([&](const Item& it) {
-                return SxArgs{P->at<char>(it, it.L.*src), it.L.nP, it.d.n, it.L.lp, P->at<char>(it, it.L.o_R64[k]),
+                return SxArgs{P->at<char>(it, it.L.*src), it.L.nP, it.L.nP, it.L.lp, P->at<char>(it, it.L.o_R64[k]),
                               it.L.lp, P->at<char>(it, it.L.*dst), it.L.nP, it.L.nP, cond ? P->flag(it, 1) : nullptr,
                               cond ? 1 : 0, -1};
             });
@@ -828,7 +830,7 @@ struct Recorder {
         };
         auto app = [&](size_t Layout::*src, int k, bool cond) {
             return each([&](const Item& it) {
-                return SxArgs{P->at<char>(it, it.L.*src), it.L.nP, it.d.n, it.L.lp, P->at<char>(it, it.L.o_R64[k]),
+                return SxArgs{P->at<char>(it, it.L.*src), it.L.nP, it.L.nP, it.L.lp, P->at<char>(it, it.L.o_R64[k]),
                               it.L.lp, P->at<char>(it, it.L.o_Zw2), it.L.nP, it.L.nP,
                               cond ? P->flag(it, 1) : nullptr, cond ? 1 : 0, -1};
             });
@@ -914,11 +916,11 @@ struct Recorder {
         sx_tall(L.tacc, L.ntr, false, each([&](const Item& it) {
                const void* Mx = it.L.tacc == DT_F64 ? (const void*)P->at<char>(it, it.L.o_M64)
                                                     : (const void*)P->at<char>(it, it.L.o_M32);
-               return SxArgs{P->at<char>(it, it.L.o_Q1), it.L.mP, it.d.m, it.L.lp, Mx, it.L.lp,
+               return SxArgs{P->at<char>(it, it.L.o_Q1), it.L.mP, it.L.mP, it.L.lp, Mx, it.L.lp,
                              P->at<char>(it, it.L.o_Phi), it.L.mP, it.L.mP, nullptr, 0, -1};
            }));
         sx(DT_F64, DT_F64, L.ntr, false, each([&](const Item& it) {
-               return SxArgs{P->at<char>(it, it.L.o_Zw), it.L.nP, it.d.n, it.L.lp, P->at<char>(it, it.L.o_Ur), it.L.lp,
+               return SxArgs{P->at<char>(it, it.L.o_Zw), it.L.nP, it.L.nP, it.L.lp, P->at<char>(it, it.L.o_Ur), it.L.lp,
                              P->at<char>(it, it.L.o_At), it.L.nP, it.L.nP, nullptr, 0, -1};
            }));
         // sign convention and outputs

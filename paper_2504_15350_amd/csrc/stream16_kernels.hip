@@ -52,24 +52,12 @@ template <> struct mma16<_Float16> {
     }
 };
 
-// Eight consecutive rows i..i+7 of column j (16-bit), zero outside [0,lim) x [0,n).
-template <bool VEC>
-__device__ __forceinline__ u16x8 load_rows8(const GLOBAL unsigned short* S, int64_t ld, int64_t lim, int64_t n,
-                                            int64_t i, int64_t j) {
-    u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (j < n) {
-        const GLOBAL unsigned short* p = S + j * ld + i;
-        if (VEC && i + 7 < lim) {
-            v = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL u16x8*>(p));  // streamed once
-        } else {
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                if (i + t < lim) v[t] = p[t];
-        }
-    }
-    return v;
+// Eight rows of one 16-bit column at any 2-byte alignment (gfx950 global loads need no more than the
+// element's), so odd leading dimensions take the same path as padded ones.
+typedef unsigned short u16x8u __attribute__((ext_vector_type(8), aligned(2)));
+__device__ __forceinline__ u16x8 load8(const GLOBAL unsigned short* p) {
+    return __builtin_nontemporal_load(reinterpret_cast<const GLOBAL u16x8u*>(p));  // streamed once
 }
-
 // ---------------------------------------------------------------------------
 // Y = S X, 16-bit S and X, FP32 Y. Workgroup: 256 rows, columns in chunks of
 // 32 (one MFMA K). Each chunk of S is staged in LDS column-major (every
@@ -83,6 +71,13 @@ __device__ __forceinline__ u16x8 load_rows8(const GLOBAL unsigned short* S, int6
 // matrix-core work. (Two transpose reads per operand in place of eight
 // 16-bit reads: 4.44 against 4.55 ms at 1048576 x 10000, lp = 128, with
 // bit-identical results.)
+// A ragged last row tile loads whole runs like any other and so takes rows past
+// m, which belong to the column's padding or to the next column; they meet only
+// output rows past m, written as zero. Only where the last column of S is in
+// the chunk (or a column is shorter than a tile) could such a run leave S: that
+// chunk's runs are moved inside and shifted back. (With per-element loads in
+// every chunk that one workgroup held the pass back: 100003 x 2000 BF16, 60
+// columns of X, ld 100008 253 -> 98 us, odd ld 100003 403 -> 102 us.)
 // ---------------------------------------------------------------------------
 constexpr int SX16_BM = 256, SX16_BK = 32;
 // LDS strides. The LDS serves 32 lanes of a 16-byte access per cycle over a 512-byte window
@@ -104,7 +99,7 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const unsigned short* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
 }
 
-template <typename T16, int NT, bool VEC>
+template <typename T16, int NT>
 __device__ __forceinline__ void sx16_body(const GLOBAL unsigned short* __restrict__ S, int64_t ldS, int64_t m,
                                           int64_t n, const GLOBAL unsigned short* __restrict__ X, int64_t ldX,
                                           GLOBAL float* __restrict__ Y, int64_t ldY, int64_t mstore, int cmax,
@@ -125,10 +120,15 @@ __device__ __forceinline__ void sx16_body(const GLOBAL unsigned short* __restric
         for (int c = 0; c < NT; ++c) acc[mt][c] = f32x4{0, 0, 0, 0};
 
     if (i0 < m) {
+        // chunks loaded and moved into place when they are staged (uniform)
+        auto edge = [&](int64_t j0) { return i0 + SX16_BM > m && (ldS < SX16_BM || j0 + SX16_BK >= n); };
         u16x8 st[4], xr[XPT];
         auto fetch = [&](int64_t j0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) st[q] = load_rows8<VEC>(S, ldS, m, n, i0 + 8 * rg, j0 + cc + 8 * q);
+            for (int q = 0; q < 4; ++q) {
+                st[q] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                if (!edge(j0) && j0 + cc + 8 * q < n) st[q] = load8(S + (j0 + cc + 8 * q) * ldS + i0 + 8 * rg);
+            }
 #pragma unroll
             for (int q = 0; q < XPT; ++q) {
                 const int ch = tid + 256 * q;
@@ -144,6 +144,12 @@ __device__ __forceinline__ void sx16_body(const GLOBAL unsigned short* __restric
         const unsigned short* asrc = tile + (8 * kg + (r16 >> 2)) * SX16_LDR + wave * 64 + 4 * (r16 & 3);
         for (int64_t j0 = 0; j0 < n; j0 += SX16_BK) {
             __syncthreads();  // previous chunk fully consumed
+            if (edge(j0)) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) st[q] = run_load<unsigned short, 8>(S, ldS, m, n, i0 + 8 * rg, j0 + cc + 8 * q);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) st[q] = run_fix<unsigned short, 8>(st[q], m, n, i0 + 8 * rg, j0 + cc + 8 * q);
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 unsigned short* dst = tile + (cc + 8 * q) * SX16_LDR + 8 * rg;
@@ -181,6 +187,10 @@ __device__ __forceinline__ void sx16_body(const GLOBAL unsigned short* __restric
             if (16 * c + r16 >= cmax) continue;
             const int64_t row = i0 + wave * 64 + 16 * mt + 4 * kg;
             GLOBAL float* py = Y + (int64_t)(16 * c + r16) * ldY + row;
+            if (i0 + SX16_BM > m) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[mt][c][v] = row + v < m ? acc[mt][c][v] : 0.0f;
+            }
             if (row + 3 < mstore) {
                 *reinterpret_cast<GLOBAL f32x4*>(py) = acc[mt][c];
             } else {
@@ -191,13 +201,13 @@ __device__ __forceinline__ void sx16_body(const GLOBAL unsigned short* __restric
         }
 }
 
-template <typename T16, int NT, bool VEC>
+template <typename T16, int NT>
 __global__ __launch_bounds__(256, 2) void k_sx16(Group<SxArgs> g) {
     if (group_skipped(g)) return;
     const int it = group_item(g.tstart, g.count, blockIdx.x);
     const SxArgs& a = g.args[it];
     const void* S = static_cast<const char*>(a.call >= 0 ? g.calls[a.call].S : a.S) + a.col0 * a.ldS * 2;
-    sx16_body<T16, NT, VEC>(gbl((const unsigned short*)S), a.ldS, a.m, a.n, gbl((const unsigned short*)a.X), a.ldX,
+    sx16_body<T16, NT>(gbl((const unsigned short*)S), a.ldS, a.m, a.n, gbl((const unsigned short*)a.X), a.ldX,
                             gbl((float*)a.Y), a.ldY, a.mstore, a.cmax > 0 ? a.cmax : 16 * NT,
                             blockIdx.x - g.tstart[it]);
 }
@@ -221,7 +231,9 @@ __global__ __launch_bounds__(256, 2) void k_sx16(Group<SxArgs> g) {
 // so every accumulator sees its k steps in row order, hi before lo. Splits
 // are interleaved (step t of split s covers rows 128 (t nsplit + s) .. +127),
 // so the workgroups of one column block read neighbouring pieces of every
-// column. Measured at 1048576 x 10000, lp = 128 (BF16, back to back): hi
+// column. A last step past row m is loaded when it is staged (one step of one
+// split; rows past m must count as zero against any padding of S); a column
+// block past column n reads column n - 1 again there and writes zeros. Measured at 1048576 x 10000, lp = 128 (BF16, back to back): hi
 // 4.71 ms against 5.15 ms for two 4-wave workgroups per CU on 128 x 128
 // blocks (bit-identical slabs), hi + lo 6.27 ms against 7.41 ms (64-row steps
 // there).
@@ -238,7 +250,7 @@ template <bool LO, int NT> struct stq16_grid {
                          WN = NT <= 2 ? 1 : !(LO && NT >= 4) ? 2 : (NT % 4 != 0 && NT % 3 == 0) ? 3 : 4;
 };
 
-template <typename T16, int NT, bool VEC, bool LO>
+template <typename T16, int NT, bool LO>
 __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restrict__ S, int64_t ldS, int64_t m,
                                            int64_t n, const GLOBAL unsigned short* __restrict__ Qh,
                                            const GLOBAL unsigned short* __restrict__ Ql, int64_t ldQ,
@@ -266,6 +278,8 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
     constexpr int SCH = (SCHT + NTHR - 1) / NTHR;      // ... per thread
     constexpr int QCH = 16 * NT * LPC;                 // Q chunks per block
     constexpr int QPT = (QCH + NTHR - 1) / NTHR;
+    static_assert(NTHR % LPC == 0, "a chunk's column advances by NTHR / LPC per q");
+    constexpr int CSTEP = NTHR / LPC;
 
     f32x4 acc[MT][NTW];
 #pragma unroll
@@ -284,29 +298,37 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
                 if (LO) qr[NQ - 1][q] = *reinterpret_cast<const GLOBAL u16x8*>(Ql + off);
             }
         }
-        if (VEC && i0 + R <= m && j0 + HB <= n) {   // whole block inside S: no per-lane bounds branches
+        if (i0 + R > m) return;  // loaded when it is staged
+        const GLOBAL unsigned short* p = S + (j0 + tid / LPC) * ldS + i0 + 8 * (tid % LPC);
+        if (j0 + HB <= n) {      // whole block inside S: no per-lane bounds
+#pragma unroll
+            for (int q = 0; q < SCH; ++q)
+                if (SCHT % NTHR == 0 || tid + NTHR * q < SCHT) sr[q] = load8(p + (int64_t)q * CSTEP * ldS);
+        } else {                 // columns past n read column n - 1 and are written as zero at the end
 #pragma unroll
             for (int q = 0; q < SCH; ++q) {
-                const int ch = tid + NTHR * q;
-                if (SCHT % NTHR == 0 || ch < SCHT)
-                    sr[q] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL u16x8*>(
-                        S + (j0 + ch / LPC) * ldS + i0 + 8 * (ch % LPC)));
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < SCH; ++q) {
-                const int ch = tid + NTHR * q;
-                if (SCHT % NTHR == 0 || ch < SCHT) sr[q] = load_rows8<VEC>(S, ldS, m, n, i0 + 8 * (ch % LPC), j0 + ch / LPC);
+                const int jl = min(tid / LPC + q * CSTEP, (int)(n - 1 - j0));
+                if (SCHT % NTHR == 0 || tid + NTHR * q < SCHT) sr[q] = load8(S + (j0 + jl) * ldS + i0 + 8 * (tid % LPC));
             }
         }
     };
     if (ib < m) fetch(ib);
     for (int64_t i0 = ib; i0 < m; i0 += stride) {
         __syncthreads();  // previous step fully consumed
+        if (i0 + R > m) {
+#pragma unroll 1
+            for (int ch = tid; ch < SCHT; ch += NTHR) {
+                const int64_t i = i0 + 8 * (ch % LPC), j = j0 + ch / LPC;
+                *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) =
+                    run_fix<unsigned short, 8>(run_load<unsigned short, 8>(S, ldS, m, n, i, j), m, n, i, j);
+            }
+        } else {
 #pragma unroll
-        for (int q = 0; q < SCH; ++q) {
-            const int ch = tid + NTHR * q;
-            if (SCHT % NTHR == 0 || ch < SCHT) *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) = sr[q];
+            for (int q = 0; q < SCH; ++q) {
+                const int ch = tid + NTHR * q;
+                if (SCHT % NTHR == 0 || ch < SCHT)
+                    *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) = sr[q];
+            }
         }
 #pragma unroll
         for (int q = 0; q < QPT; ++q) {
@@ -349,9 +371,13 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
 #pragma unroll
         for (int c = 0; c < NTW; ++c) {
             const int nt = NTW * wn + c;
+            const int64_t j = j0 + 16 * MT * wm + 16 * t + 4 * kg;
+            if (j0 + HB > n) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[t][c][v] = j + v < n ? acc[t][c][v] : 0.0f;
+            }
             if (NT % WN == 0 || nt < NT)
-                *reinterpret_cast<GLOBAL f32x4*>(zp + (int64_t)(16 * nt + r16) * nP + j0 + 16 * MT * wm + 16 * t +
-                                                 4 * kg) = acc[t][c];
+                *reinterpret_cast<GLOBAL f32x4*>(zp + (int64_t)(16 * nt + r16) * nP + j) = acc[t][c];
         }
 }
 
@@ -360,7 +386,7 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
 // first workgroup are multiples of 8, local workgroup b takes tile
 // (b mod 8) T / 8 + b / 8, so each XCD holds every column block of a range of
 // splits and a split's Q rows are fetched into one L2 only.
-template <typename T16, int NT, bool VEC, bool LO>
+template <typename T16, int NT, bool LO>
 __global__ __launch_bounds__((64 * stq16_grid<LO, NT>::WM * stq16_grid<LO, NT>::WN)) void k_stq16(Group<StqArgs> g) {
     if (group_skipped(g)) return;
     const int it = group_item(g.tstart, g.count, blockIdx.x);
@@ -368,7 +394,7 @@ __global__ __launch_bounds__((64 * stq16_grid<LO, NT>::WM * stq16_grid<LO, NT>::
     const void* S = a.call >= 0 ? g.calls[a.call].S : a.S;
     const int local = blockIdx.x - g.tstart[it], ntl = a.ncb * a.nsplit;
     const int tile = ((ntl & 7) == 0 && (g.tstart[it] & 7) == 0) ? (local & 7) * (ntl >> 3) + (local >> 3) : local;
-    stq16_body<T16, NT, VEC, LO>(gbl((const unsigned short*)S), a.ldS, a.m, a.n, gbl((const unsigned short*)a.Q),
+    stq16_body<T16, NT, LO>(gbl((const unsigned short*)S), a.ldS, a.m, a.n, gbl((const unsigned short*)a.Q),
                                  gbl((const unsigned short*)a.Ql), a.ldQ, gbl((float*)a.Zp), a.nP, a.nsplit, a.ncb,
                                  tile);
 }
@@ -410,59 +436,46 @@ static Group<A> mkgroup16(const GroupLaunch<A>& L) {
     return g;
 }
 
-template <typename T16, int NT>
-static hipError_t sx16_nt(const GroupLaunch<SxArgs>& L, bool vec, hipStream_t st) {
-    if (vec)
-        hipLaunchKernelGGL((k_sx16<T16, NT, true>), dim3(L.tiles), dim3(256), 0, st, mkgroup16(L));
-    else
-        hipLaunchKernelGGL((k_sx16<T16, NT, false>), dim3(L.tiles), dim3(256), 0, st, mkgroup16(L));
-    return hipGetLastError();
-}
-
-template <typename T16, int NT, bool LO>
-static hipError_t stq16_nt(const GroupLaunch<StqArgs>& L, bool vec, hipStream_t st) {
-    const dim3 block(64 * stq16_grid<LO, NT>::WM * stq16_grid<LO, NT>::WN);
-    if (vec)
-        hipLaunchKernelGGL((k_stq16<T16, NT, true, LO>), dim3(L.tiles), block, 0, st, mkgroup16(L));
-    else
-        hipLaunchKernelGGL((k_stq16<T16, NT, false, LO>), dim3(L.tiles), block, 0, st, mkgroup16(L));
-    return hipGetLastError();
-}
-
 template <typename T16>
-static hipError_t sx16_dispatch(int nt, const GroupLaunch<SxArgs>& L, bool vec, hipStream_t st) {
+static hipError_t sx16_dispatch(int nt, const GroupLaunch<SxArgs>& L, hipStream_t st) {
     switch (nt) {
-#define RPOD_C(K) case K: return sx16_nt<T16, K>(L, vec, st);
+#define RPOD_C(K) \
+    case K: hipLaunchKernelGGL((k_sx16<T16, K>), dim3(L.tiles), dim3(256), 0, st, mkgroup16(L)); break;
         RPOD_C(1) RPOD_C(2) RPOD_C(3) RPOD_C(4) RPOD_C(5) RPOD_C(6) RPOD_C(7) RPOD_C(8)
 #undef RPOD_C
         default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
 }
 
 template <typename T16, bool LO>
-static hipError_t stq16_dispatch(int nt, const GroupLaunch<StqArgs>& L, bool vec, hipStream_t st) {
+static hipError_t stq16_dispatch(int nt, const GroupLaunch<StqArgs>& L, hipStream_t st) {
     switch (nt) {
-#define RPOD_C(K) case K: return stq16_nt<T16, K, LO>(L, vec, st);
+#define RPOD_C(K)                                                                                                 \
+    case K:                                                                                                       \
+        hipLaunchKernelGGL((k_stq16<T16, K, LO>), dim3(L.tiles),                                                  \
+                           dim3(64 * stq16_grid<LO, K>::WM * stq16_grid<LO, K>::WN), 0, st, mkgroup16(L));        \
+        break;
         RPOD_C(1) RPOD_C(2) RPOD_C(3) RPOD_C(4) RPOD_C(5) RPOD_C(6) RPOD_C(7) RPOD_C(8)
 #undef RPOD_C
         default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
 }
 
 int stq16_block_cols(bool) { return STQ16_HB; }
 int stq16_rows_per_step(bool) { return STQ16_R; }
 
-hipError_t launch_sx16(int tin, int nt, bool vec, const GroupLaunch<SxArgs>& L, hipStream_t st) {
-    if (tin == DT_BF16) return sx16_dispatch<__bf16>(nt, L, vec, st);
-    if (tin == DT_F16) return sx16_dispatch<_Float16>(nt, L, vec, st);
+hipError_t launch_sx16(int tin, int nt, bool /*vec*/, const GroupLaunch<SxArgs>& L, hipStream_t st) {
+    if (tin == DT_BF16) return sx16_dispatch<__bf16>(nt, L, st);
+    if (tin == DT_F16) return sx16_dispatch<_Float16>(nt, L, st);
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_stq16(int tin, int nt, bool lo, bool vec, const GroupLaunch<StqArgs>& L, hipStream_t st) {
-    if (tin == DT_BF16)
-        return lo ? stq16_dispatch<__bf16, true>(nt, L, vec, st) : stq16_dispatch<__bf16, false>(nt, L, vec, st);
+hipError_t launch_stq16(int tin, int nt, bool lo, bool /*vec*/, const GroupLaunch<StqArgs>& L, hipStream_t st) {
+    if (tin == DT_BF16) return lo ? stq16_dispatch<__bf16, true>(nt, L, st) : stq16_dispatch<__bf16, false>(nt, L, st);
     if (tin == DT_F16)
-        return lo ? stq16_dispatch<_Float16, true>(nt, L, vec, st) : stq16_dispatch<_Float16, false>(nt, L, vec, st);
+        return lo ? stq16_dispatch<_Float16, true>(nt, L, st) : stq16_dispatch<_Float16, false>(nt, L, st);
     return hipErrorInvalidValue;
 }
 

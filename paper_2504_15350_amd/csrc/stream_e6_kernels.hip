@@ -72,23 +72,10 @@ __device__ __forceinline__ void mma6(const e6_u16x8& ah, const e6_u16x8& am, con
     acc = mma_bf16(ah, bh, s);
 }
 
-// Four consecutive rows i..i+3 of column j (FP32), rows >= lim or columns >= n read 0.
-template <bool VEC>
-__device__ __forceinline__ f32x4 e6_rows4(const GLOBAL float* S, int64_t ld, int64_t lim, int64_t n, int64_t i,
-                                          int64_t j) {
-    f32x4 v = {0, 0, 0, 0};
-    if (j < n) {
-        const GLOBAL float* p = S + j * ld + i;
-        if (VEC && i + 3 < lim) {
-            v = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL f32x4*>(p));  // streamed once
-        } else {
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (i + t < lim) v[t] = p[t];
-        }
-    }
-    return v;
-}
+// A 16-byte load at any 4-byte alignment: gfx950 global loads need no more, so odd leading
+// dimensions of S take the same path as padded ones (100003 x 2000, ld 100003, 60 columns of X: S X
+// 283 -> 218 us against four scalar loads).
+typedef float e6_f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // ---------------------------------------------------------------------------
 // Y = S X. Workgroup = 4 waves = 256 rows. Per 32-column step lane (r, g)
@@ -107,7 +94,7 @@ constexpr int E6_XLD = 40;  // halfwords per staged X column (32 rows + pad)
 // before the matrix-core work (with four steps per workgroup every exposed load latency counts:
 // 1048576 x 128 times 128 x 128, 367 against 393 us); long passes over S keep the loads after the
 // matrix-core work (262144 x 5000 with 64 columns: 1.07 against 1.12 ms).
-template <int NT, bool VEC, bool EN = false, bool TALL = false>
+template <int NT, bool EN = false, bool TALL = false>
 __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, int64_t m, int64_t n,
                                            const GLOBAL float* __restrict__ X, int64_t ldX,
                                            GLOBAL float* Y, int64_t ldY, int64_t mstore, int cmax, int64_t bx,
@@ -120,7 +107,13 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
     const int r16 = lane & 15, g = lane >> 4;
     const int64_t iw = bx * 256 + wave * 64;
     const int64_t irow = iw + 4 * r16;
-    const bool fast = VEC && iw + 64 <= m;  // whole wave in range: unguarded vector loads
+    // Unguarded vector loads, a uniform base per column plus a 32-bit lane offset. A wave with rows past
+    // m takes whole runs too (rows of the column's padding or of the next column, which meet only
+    // output rows past m, written as zero), except where the last column of S is in the step, whose
+    // runs could leave S, or a column is shorter than a tile.
+    const bool inside = iw + 64 <= m, fast = (inside || ldS >= 256) && ldS < ((int64_t)1 << 25);
+    auto plain = [&](int64_t j0) { return fast && j0 + 32 <= (inside ? n : n - 1); };
+    const uint32_t so = (uint32_t)(8 * g) * (uint32_t)(4 * ldS) + (uint32_t)(4 * irow);
     f32x4 acc[4][NT];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -128,14 +121,14 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
         for (int c = 0; c < NT; ++c) acc[t][c] = f32x4{0, 0, 0, 0};
     f32x4 sv[8];
     auto load_s = [&](int64_t j0) {
-        if (fast && j0 + 32 <= n) {
-            const GLOBAL float* p = S + (j0 + 8 * g) * ldS + irow;
+        if (plain(j0)) {
+            const GLOBAL char* p = reinterpret_cast<const GLOBAL char*>(S + j0 * ldS);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                sv[i] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL f32x4*>(p + i * ldS));
+                sv[i] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL e6_f32x4u*>(p + 4 * i * ldS + so));
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sv[i] = e6_rows4<VEC>(S, ldS, m, n, irow, j0 + 8 * g + i);
+            for (int i = 0; i < 8; ++i) sv[i] = run_load<float, 4>(S, ldS, m, n, irow, j0 + 8 * g + i);
         }
     };
     f32x4 xr[XPT];
@@ -163,19 +156,26 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
             }
         }
     };
-    load_s(0);  // rows >= m read as 0 (guarded path)
+    load_s(0);
     load_x(0);
     put_x(0);
     int buf = 0;
     double sq = 0.0;  // EN: sum of the squares of this lane's S entries (FP32 per step, FP64 across steps)
     for (int64_t j0 = 0; j0 < n; j0 += 32) {  // uniform trip count: the barriers below are reached by all waves
         const bool more = j0 + 32 < n;
+        if (!plain(j0)) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sv[i] = run_fix<float, 4>(sv[i], m, n, irow, j0 + 8 * g + i);
+        }
         if constexpr (EN) {
             float p = 0.0f;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) p = fmaf(sv[i][t], sv[i][t], p);
+                for (int t = 0; t < 4; ++t) {
+                    const float x = inside || irow + t < m ? sv[i][t] : 0.0f;
+                    p = fmaf(x, x, p);
+                }
             sq += (double)p;
         }
         e6_u16x8 ah[4], am[4], al[4];
@@ -212,13 +212,17 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int64_t row = iw + 4 * (4 * g + v);
+            f32x4 o{acc[0][c][v], acc[1][c][v], acc[2][c][v], acc[3][c][v]};
+            if (!inside) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[t] = row + t < m ? o[t] : 0.0f;
+            }
             if (row + 3 < mstore) {
-                *reinterpret_cast<GLOBAL f32x4*>(py + row) =
-                    f32x4{acc[0][c][v], acc[1][c][v], acc[2][c][v], acc[3][c][v]};
+                *reinterpret_cast<GLOBAL f32x4*>(py + row) = o;
             } else {
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
-                    if (row + t < mstore) py[row + t] = acc[t][c][v];
+                    if (row + t < mstore) py[row + t] = o[t];
             }
         }
     }
@@ -226,7 +230,7 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
 
 // EN: the energy report's variant (also each tile's sum of squares of S, in
 // a fixed order: per lane, then a tree over the workgroup)
-template <int NT, bool VEC, bool EN = false, bool TALL = false>
+template <int NT, bool EN = false, bool TALL = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2 : 1, 2))) void k_sx_e6(
     Group<SxArgs> g) {
     if (group_skipped(g)) return;
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2
     if constexpr (EN) {
         __shared__ double red[256];
         double sq = 0.0;
-        sx_e6_body<NT, VEC, true>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.X), a.ldX,
+        sx_e6_body<NT, true>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.X), a.ldX,
                                   gbl((float*)a.Y), a.ldY, a.mstore, a.cmax > 0 ? a.cmax : 16 * NT,
                                   blockIdx.x - g.tstart[it], xs, &sq);
         red[threadIdx.x] = sq;
@@ -249,7 +253,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2
         }
         if (threadIdx.x == 0 && a.fpart != nullptr) a.fpart[blockIdx.x - g.tstart[it]] = red[0];
     } else {
-        sx_e6_body<NT, VEC, false, TALL>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.X), a.ldX,
+        sx_e6_body<NT, false, TALL>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.X), a.ldX,
                                          gbl((float*)a.Y), a.ldY, a.mstore, a.cmax > 0 ? a.cmax : 16 * NT,
                                          blockIdx.x - g.tstart[it], xs);
     }
@@ -277,7 +281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2
 // ---------------------------------------------------------------------------
 constexpr int E6_R = 32, E6_LDS = E6_R, E6_LDQ = E6_R, E6_HB = 256;
 
-template <int NT, bool VEC>
+template <int NT>
 __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, int64_t ldS, int64_t m, int64_t n,
                                             const GLOBAL float* __restrict__ Q, int64_t ldQ,
                                             GLOBAL float* __restrict__ Zp, int64_t nP, int nsplit, int ncb,
@@ -307,44 +311,56 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
     f32x4 qr[QPT];
     // chunk q of a thread: column j0 + tid / CPC + q (256 / CPC), rows 4 (tid mod CPC) .. +3 of the step
     constexpr int CSTEP = 256 / CPC;
-    const int64_t jt = j0 + tid / CPC;
-    const GLOBAL float* sbase = S + jt * ldS + 4 * (tid % CPC);
+    const GLOBAL float* sbase = S + (j0 + tid / CPC) * ldS + 4 * (tid % CPC);
     auto fetch = [&](int64_t i0) {
-        if (VEC && i0 + R <= m) {  // whole step in range: one unguarded vector load per chunk
+        if (j0 + HB <= n) {  // whole step in range: one unguarded vector load per chunk
             const GLOBAL float* p = sbase + i0;
 #pragma unroll
             for (int q = 0; q < SPT; ++q)
-                sr[q] = (jt + CSTEP * q < n)
-                            ? __builtin_nontemporal_load(reinterpret_cast<const GLOBAL f32x4*>(p + CSTEP * q * ldS))
-                            : f32x4{0, 0, 0, 0};
-        } else {
+                sr[q] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL f32x4*>(p + CSTEP * q * ldS));
+        } else {  // columns past n read column n - 1 and are written as zero at the end
 #pragma unroll
             for (int q = 0; q < SPT; ++q) {
-                const int ch = tid + 256 * q;
-                sr[q] = e6_rows4<VEC>(S, ldS, m, n, i0 + 4 * (ch % CPC), j0 + ch / CPC);
+                const int jl = min(tid / CPC + CSTEP * q, (int)(n - 1 - j0));
+                sr[q] = __builtin_nontemporal_load(
+                    reinterpret_cast<const GLOBAL f32x4*>(S + (j0 + jl) * ldS + i0 + 4 * (tid % CPC)));
             }
         }
+    };
+    auto fetch_q = [&](int64_t i0) {
 #pragma unroll
         for (int q = 0; q < QPT; ++q) {
             const int ch = tid + 256 * q;
-            if (ch < QCH)
+            if (QCH % 256 == 0 || ch < QCH)
                 qr[q] = *reinterpret_cast<const GLOBAL f32x4*>(Q + (int64_t)(ch / QCPC) * ldQ + i0 + 4 * (ch % QCPC));
         }
     };
     static_assert(CPC == 8 && QCPC == 8, "swizzle patterns assume 32-row steps");
-    auto put = [&]() {
+    auto put_s = [&]() {
 #pragma unroll
         for (int q = 0; q < SPT; ++q) {
             const int ch = tid + 256 * q, col = ch / CPC;
             *reinterpret_cast<f32x4*>(ss + col * LD + 4 * ((ch % CPC) ^ ((col >> 1) & 7))) = sr[q];
         }
+    };
+    // a last step past row m (rows past m must count as zero against any padding of S)
+    auto put_edge = [&](int64_t i0) {
+#pragma unroll
+        for (int q = 0; q < SPT; ++q)
+            sr[q] = run_load<float, 4>(S, ldS, m, n, i0 + 4 * (tid % CPC), j0 + tid / CPC + CSTEP * q);
+#pragma unroll
+        for (int q = 0; q < SPT; ++q)
+            sr[q] = run_fix<float, 4>(sr[q], m, n, i0 + 4 * (tid % CPC), j0 + tid / CPC + CSTEP * q);
+        put_s();
+    };
+    auto put_q = [&]() {
         // Q chunk (rows 4 k .. 4 k + 3 of a column) -> 8 bytes of each part, in
         // half k mod 2 of the part's 16-byte chunk k / 2
         typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
         for (int q = 0; q < QPT; ++q) {
             const int ch = tid + 256 * q, col = ch / QCPC, k = ch % QCPC;
-            if (ch < QCH) {
+            if (QCH % 256 == 0 || ch < QCH) {
                 unsigned h0, m0, l0, h1, m1, l1;
                 split_pair(qr[q][0], qr[q][1], h0, m0, l0);
                 split_pair(qr[q][2], qr[q][3], h1, m1, l1);
@@ -356,12 +372,7 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
         }
     };
 
-    if (ib < m) fetch(ib);
-    for (int64_t i0 = ib; i0 < m; i0 = next(i0)) {
-        __syncthreads();  // previous step consumed
-        put();
-        __syncthreads();
-        if (next(i0) < m) fetch(next(i0));  // in flight during the matrix-core work
+    auto work = [&]() {
         e6_u16x8 ah[U], am[U], al[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -380,6 +391,27 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
 #pragma unroll
             for (int u = 0; u < U; ++u) mma6(ah[u], am[u], al[u], bh, bm, bl, acc[u][c]);
         }
+    };
+    int64_t i0 = ib;
+    if (i0 < m) fetch_q(i0);
+    if (i0 + R <= m) fetch(i0);
+    while (i0 + R <= m) {
+        const int64_t nx = next(i0);
+        __syncthreads();  // previous step consumed
+        put_s();
+        put_q();
+        __syncthreads();
+        if (nx < m) fetch_q(nx);  // in flight during the matrix-core work
+        if (nx + R <= m) fetch(nx);
+        work();
+        i0 = nx;
+    }
+    if (i0 < m) {
+        __syncthreads();
+        put_edge(i0);
+        put_q();
+        __syncthreads();
+        work();
     }
     // D[4 g + v][r]: S column j0 + 16 U w + 16 u + 4 g + v, Q column 16 c + r; the
     // slab keeps the FP32 accumulators as they are (summed in FP64 afterwards)
@@ -387,17 +419,201 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int c = 0; c < NT; ++c)
-            *reinterpret_cast<GLOBAL f32x4*>(zp + (int64_t)(16 * c + r16) * nP + j0 + 16 * U * wave + 16 * u + 4 * g) =
-                acc[u][c];
+        for (int c = 0; c < NT; ++c) {
+            const int64_t j = j0 + 16 * U * wave + 16 * u + 4 * g;
+            if (j0 + HB > n) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[u][c][v] = j + v < n ? acc[u][c][v] : 0.0f;
+            }
+            *reinterpret_cast<GLOBAL f32x4*>(zp + (int64_t)(16 * c + r16) * nP + j) = acc[u][c];
+        }
 }
 
-template <int NT, bool VEC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2 : 1, 2))) void k_stq_e6(
+// ---------------------------------------------------------------------------
+// The same product where S's columns do not start on 128-byte lines (odd or
+// padded leading dimensions): a 32-row run of a column then straddles two lines,
+// so the workgroup takes its units of 64 rows in two steps of 128 columns x 64
+// rows (runs of 256 bytes, three lines instead of four). The accumulation
+// order of every entry is the one above. 100003 x 2000, 60 columns, ld 100003 /
+// 100008: 293 / 268 -> 240 / 232 us; with columns on lines the steps above are
+// the faster (131072 x 2000: 240 against 264 us), because here a staged Q
+// operand serves two column tiles instead of four.
+// The S block (128 x 64, FP32) of a step and once per unit the parts of the Q
+// block (64 x 16 NT) are staged in LDS column-major. Wave w owns columns 32 w ..
+// 32 w + 31 of each half (two column tiles). S column c holds its 16-byte
+// chunk k at k ^ sw_s(c), Q column c at k ^ sw_q(c): the 32 lanes one LDS cycle
+// serves (16 columns, two g) touch every 16-byte slot of its 512-byte window once.
+// ---------------------------------------------------------------------------
+constexpr int E6U_R = 64, E6U_HC = 128;
+
+__device__ __forceinline__ int sw_s(int c) { return ((c >> 1) & 1) | (((c >> 1) & 6) << 1); }  // of 16 chunks
+__device__ __forceinline__ int sw_q(int c) { return ((c >> 2) & 3) << 1; }                     // of 8 chunks
+
+template <int NT>
+__device__ __forceinline__ void stq_e6u_body(const GLOBAL float* __restrict__ S, int64_t ldS, int64_t m, int64_t n,
+                                           const GLOBAL float* __restrict__ Q, int64_t ldQ,
+                                           GLOBAL float* __restrict__ Zp, int64_t nP, int nsplit, int ncb,
+                                           int tile, float* ss, unsigned short* qs) {
+    constexpr int R = E6U_R, U = 2;             // column tiles per wave and half
+    constexpr int CPC = R / 4;                  // 16-byte FP32 chunks per column
+    constexpr int SPT = E6U_HC * CPC / 256;      // S chunks per thread and step
+    constexpr int QCH = 16 * NT * CPC;          // Q chunks per unit
+    constexpr int QPT = QCH / 256;
+    constexpr int QPART = 16 * NT * R;          // halfwords per staged part
+    const int cb = tile % ncb, sp = tile / ncb;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int64_t j0 = (int64_t)cb * E6_HB;
+
+    f32x4 acc[2][U][NT];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < NT; ++c) acc[h][u][c] = f32x4{0, 0, 0, 0};
+
+    f32x4 sr[SPT];
+    f32x4 qr[QPT];
+    // chunk q of a thread: column (of the half) tid / CPC + q (256 / CPC), rows 4 (tid mod CPC) .. + 3.
+    // Addresses are a uniform base per chunk plus one 32-bit offset per thread (narrow: it fits).
+    constexpr int CSTEP = 256 / CPC;
+    const int tc = tid / CPC, tk = tid % CPC;
+    const bool narrow = ldS < ((int64_t)1 << 26);
+    const uint32_t so = (uint32_t)tc * (uint32_t)(4 * ldS) + 16 * tk, qo = (uint32_t)tc * (uint32_t)(4 * ldQ) + 16 * tk;
+    const int sws = sw_s(tc), swq = sw_q(tc);  // of every column tc + 16 q
+    auto fetch_s = [&](int64_t i0, int h) {
+        const int64_t jh = j0 + E6U_HC * h;
+        if (i0 + R > m) return;  // a last unit past row m is loaded when it is staged
+        if (narrow && jh + E6U_HC <= n) {  // the whole step in range: unguarded vector loads
+            const GLOBAL char* p = reinterpret_cast<const GLOBAL char*>(S + jh * ldS + i0);
+#pragma unroll
+            for (int q = 0; q < SPT; ++q)
+                sr[q] = __builtin_nontemporal_load(
+                    reinterpret_cast<const GLOBAL e6_f32x4u*>(p + 4 * CSTEP * q * ldS + so));
+        } else {  // columns past n read column n - 1 and are written as zero at the end
+#pragma unroll
+            for (int q = 0; q < SPT; ++q) {
+                const int64_t j = jh + tc + CSTEP * q;
+                sr[q] = __builtin_nontemporal_load(
+                    reinterpret_cast<const GLOBAL e6_f32x4u*>(S + (j < n ? j : n - 1) * ldS + i0 + 4 * tk));
+            }
+        }
+    };
+    auto fetch_q = [&](int64_t i0) {
+        const GLOBAL char* p = reinterpret_cast<const GLOBAL char*>(Q + i0);
+#pragma unroll
+        for (int q = 0; q < QPT; ++q)
+            qr[q] = *reinterpret_cast<const GLOBAL f32x4*>(p + 4 * CSTEP * q * ldQ + qo);
+    };
+    auto put_s = [&](int64_t i0, int h) {
+        float* d = ss + tc * R + 4 * (tk ^ sws);
+        if (i0 + R > m) {
+            int64_t j = j0 + E6U_HC * h + tc;
+#pragma unroll 1
+            for (int q = 0; q < SPT; q += 2, j += 2 * CSTEP) {
+                f32x4 a = run_load<float, 4>(S, ldS, m, n, i0 + 4 * tk, j);
+                f32x4 b = run_load<float, 4>(S, ldS, m, n, i0 + 4 * tk, j + CSTEP);
+                a = run_fix<float, 4>(a, m, n, i0 + 4 * tk, j);
+                b = run_fix<float, 4>(b, m, n, i0 + 4 * tk, j + CSTEP);
+                *reinterpret_cast<f32x4*>(d + CSTEP * q * R) = a;
+                *reinterpret_cast<f32x4*>(d + CSTEP * (q + 1) * R) = b;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < SPT; ++q) *reinterpret_cast<f32x4*>(d + CSTEP * q * R) = sr[q];
+        }
+    };
+    // Q chunk (rows 4 k .. 4 k + 3 of a column) -> 8 bytes of each part, in half k mod 2 of the
+    // part's 16-byte chunk k / 2
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    auto put_q = [&]() {
+        unsigned short* d = qs + tc * R + 8 * ((tk >> 1) ^ swq) + 4 * (tk & 1);
+#pragma unroll
+        for (int q = 0; q < QPT; ++q) {
+            const int o = CSTEP * q * R;
+            unsigned h0, m0, l0, h1, m1, l1;
+            split_pair(qr[q][0], qr[q][1], h0, m0, l0);
+            split_pair(qr[q][2], qr[q][3], h1, m1, l1);
+            *reinterpret_cast<u32x2*>(d + 2 * QPART + o) = u32x2{l0, l1};
+            *reinterpret_cast<u32x2*>(d + o) = u32x2{h0, h1};
+            *reinterpret_cast<u32x2*>(d + QPART + o) = u32x2{m0, m1};
+        }
+    };
+    // the staged half times the staged unit of Q, 32 rows at a time
+    auto half = [&](f32x4 (&ac)[U][NT]) {
+#pragma unroll 1
+        for (int kh = 0; kh < 2; ++kh) {
+            const float* src = ss + (32 * wave + r16) * R;
+            const int c0 = (8 * kh + 2 * g) ^ sw_s(r16), cq = (4 * kh + g) ^ sw_q(r16);
+            f32x4 x0[U], x1[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                x0[u] = *reinterpret_cast<const f32x4*>(src + 16 * u * R + 4 * c0);
+                x1[u] = *reinterpret_cast<const f32x4*>(src + 16 * u * R + 4 * (c0 ^ 1));
+            }
+            const unsigned short* qp0 = qs + r16 * R + 8 * cq;
+            e6_u16x8 ah[U], am[U], al[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) split8(x0[u], x1[u], ah[u], am[u], al[u]);
+#pragma unroll
+            for (int c = 0; c < NT; ++c) {
+                const unsigned short* qp = qp0 + 16 * c * R;
+                const e6_u16x8 bh = *reinterpret_cast<const e6_u16x8*>(qp);
+                const e6_u16x8 bm = *reinterpret_cast<const e6_u16x8*>(qp + QPART);
+                const e6_u16x8 bl = *reinterpret_cast<const e6_u16x8*>(qp + 2 * QPART);
+#pragma unroll
+                for (int u = 0; u < U; ++u) mma6(ah[u], am[u], al[u], bh, bm, bl, ac[u][c]);
+            }
+        }
+    };
+
+    const int64_t ib = (int64_t)sp * R, jump = (int64_t)nsplit * R;
+    if (ib < m) {
+        fetch_s(ib, 0);
+        fetch_q(ib);
+    }
+    for (int64_t i0 = ib; i0 < m; i0 += jump) {
+        __syncthreads();  // the previous unit is consumed
+        put_s(i0, 0);
+        put_q();
+        fetch_s(i0, 1);  // in flight during the matrix-core work
+        __syncthreads();
+        half(acc[0]);
+        __syncthreads();
+        put_s(i0, 1);
+        if (i0 + jump < m) {
+            fetch_s(i0 + jump, 0);
+            fetch_q(i0 + jump);
+        }
+        __syncthreads();
+        half(acc[1]);
+    }
+    // D[4 g + v][r]: S column j0 + 128 h + 32 w + 16 u + 4 g + v, Q column 16 c + r; the slab keeps the
+    // FP32 accumulators as they are (summed in FP64 afterwards)
+    GLOBAL float* zp = Zp + (int64_t)sp * nP * (16 * NT);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < NT; ++c) {
+                const int64_t j = j0 + E6U_HC * h + 32 * wave + 16 * u + 4 * g;
+                if (j0 + E6_HB > n) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[h][u][c][v] = j + v < n ? acc[h][u][c][v] : 0.0f;
+                }
+                *reinterpret_cast<GLOBAL f32x4*>(zp + (int64_t)(16 * c + r16) * nP + j) = acc[h][u][c];
+            }
+}
+
+// LINES: S's columns start on 128-byte lines
+template <int NT, bool LINES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= (LINES ? 4 : 6) ? 2 : 1, 2))) void k_stq_e6(
     Group<StqArgs> g) {
     if (group_skipped(g)) return;
-    __shared__ __attribute__((aligned(16))) float ss[E6_HB * E6_LDS];
-    __shared__ __attribute__((aligned(16))) unsigned short qs[3 * 16 * NT * E6_LDQ];
+    __shared__ __attribute__((aligned(16))) float ss[E6_HB * E6_LDS];  // = 128 x 64
+    __shared__ __attribute__((aligned(16))) unsigned short qs[3 * 16 * NT * (LINES ? E6_LDQ : E6U_R)];
     const int it = group_item(g.tstart, g.count, blockIdx.x);
     const StqArgs& a = g.args[it];
     const void* S = a.call >= 0 ? g.calls[a.call].S : a.S;
@@ -405,7 +621,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2
     // multiple of 8) takes tile (b mod 8) T / 8 + b / 8 of the item's T
     const int local = blockIdx.x - g.tstart[it], ntl = a.ncb * a.nsplit;
     const int tile = ((ntl & 7) == 0 && (g.tstart[it] & 7) == 0) ? (local & 7) * (ntl >> 3) + (local >> 3) : local;
-    stq_e6_body<NT, VEC>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.Q), a.ldQ, gbl((float*)a.Zp),
+    if constexpr (LINES)
+        stq_e6_body<NT>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.Q), a.ldQ, gbl((float*)a.Zp),
+                        a.nP, a.nsplit, a.ncb, tile, ss, qs);
+    else
+        stq_e6u_body<NT>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.Q), a.ldQ, gbl((float*)a.Zp),
                          a.nP, a.nsplit, a.ncb, tile, ss, qs);
 }
 
@@ -425,41 +645,33 @@ static Group<A> mke6(const GroupLaunch<A>& L) {
 }
 
 template <int NT>
-static hipError_t sxe6_nt(const GroupLaunch<SxArgs>& L, bool vec, bool en, bool tall, hipStream_t st) {
-    if (tall && vec && !en) {
-        hipLaunchKernelGGL((k_sx_e6<NT, true, false, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
-        return hipGetLastError();
-    }
-    if (en) {
-        if (vec)
-            hipLaunchKernelGGL((k_sx_e6<NT, true, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
-        else
-            hipLaunchKernelGGL((k_sx_e6<NT, false, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
-    } else if (vec) {
+static hipError_t sxe6_nt(const GroupLaunch<SxArgs>& L, bool en, bool tall, hipStream_t st) {
+    if (tall)
+        hipLaunchKernelGGL((k_sx_e6<NT, false, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
+    else if (en)
         hipLaunchKernelGGL((k_sx_e6<NT, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
-    } else {
-        hipLaunchKernelGGL((k_sx_e6<NT, false>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
-    }
-    return hipGetLastError();
-}
-
-template <int NT>
-static hipError_t stqe6_nt(const GroupLaunch<StqArgs>& L, bool vec, hipStream_t st) {
-    if (vec)
-        hipLaunchKernelGGL((k_stq_e6<NT, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
     else
-        hipLaunchKernelGGL((k_stq_e6<NT, false>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
+        hipLaunchKernelGGL((k_sx_e6<NT>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
     return hipGetLastError();
 }
 
-hipError_t launch_sx_e6(int nt, bool vec, bool en, bool tall, const GroupLaunch<SxArgs>& L, hipStream_t st) {
+hipError_t launch_sx_e6(int nt, bool /*vec*/, bool en, bool tall, const GroupLaunch<SxArgs>& L, hipStream_t st) {
     switch (nt) {
-#define RPOD_E6_CASE(K) case K: return sxe6_nt<K>(L, vec, en, tall, st);
+#define RPOD_E6_CASE(K) case K: return sxe6_nt<K>(L, en, tall, st);
         RPOD_E6_CASE(1) RPOD_E6_CASE(2) RPOD_E6_CASE(3) RPOD_E6_CASE(4)
         RPOD_E6_CASE(5) RPOD_E6_CASE(6) RPOD_E6_CASE(7) RPOD_E6_CASE(8)
 #undef RPOD_E6_CASE
         default: return hipErrorInvalidValue;
     }
+}
+
+template <int NT>
+static hipError_t stqe6_nt(const GroupLaunch<StqArgs>& L, bool lines, hipStream_t st) {
+    if (lines)
+        hipLaunchKernelGGL((k_stq_e6<NT, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
+    else
+        hipLaunchKernelGGL((k_stq_e6<NT, false>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
+    return hipGetLastError();
 }
 
 hipError_t launch_stq_e6(int nt, bool vec, const GroupLaunch<StqArgs>& L, hipStream_t st) {

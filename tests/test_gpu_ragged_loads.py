@@ -1,0 +1,49 @@
+"""The passes over S load whole vectors at any alignment and take rows past m from
+the padding or the next column: row remainders of a tile, a step and a vector,
+matrices with fewer rows than a vector or columns shorter than a tile, and
+leading dimensions on and off the lines. The padding holds NaN and S starts one
+element past an aligned address where that is allowed. Against the oracle, with
+the tolerances of the parity tests."""
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import rpod as orpod
+from test_gpu_parity import DEV, compare, round_to, run_gpu, sketch_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16, torch.float64])
+@pytest.mark.parametrize("m,n,r,p,ld", [
+    (2, 3, 1, 1, 2),             # fewer rows than any vector
+    (3, 40, 2, 1, 5),            # ... and padding shorter than one
+    (7, 300, 5, 2, 7),           # columns shorter than a tile, more than one column block
+    (9, 33, 6, 3, 16),
+    (65, 31, 12, 4, 66),
+    (130, 257, 20, 12, 160),     # columns on lines, NaN rows past m
+    (255, 64, 20, 12, 255),      # one row short of a tile
+    (257, 700, 40, 9, 288),
+    (513, 255, 70, 10, 515),     # one row into a third tile
+    (1031, 129, 100, 20, 1032),
+    (4127, 513, 110, 18, 4127),  # eight column tiles, one column into a third block
+])
+def test_ragged(m, n, r, p, ld, dtype):
+    if dtype == torch.bfloat16 and r == 110:
+        pytest.skip("the cut after mode 110 lies in BF16's rounding noise (relative gap 4.5e-3, sin 6.6e-3 with "
+                    "or without whole-vector loads): the subspace bound does not apply")
+    g = synth.lowrank_exp(m, n, decay=0.08, noise_std=1e-5, seed=3 * m + n, K=min(m, n))
+    Sr = round_to(g["St"], dtype)
+    odd = ld % (8 if dtype in (torch.bfloat16, torch.float16) else 4) != 0  # no 16-byte alignment asked for
+    buf = torch.full((n * ld + 1,), float("nan"), dtype=dtype)
+    Sv = buf[1 if odd else 0:][:n * ld].view(n, ld)
+    Sv[:, :m] = Sr
+    dbuf = buf.to(DEV)
+    Sd = dbuf[1 if odd else 0:][:n * ld].view(n, ld)
+    print(f"[case] m={m} n={n} r={r} p={p} ld={ld} {dtype}", flush=True)
+    gpu = run_gpu(Sd, m, n, r, p, 1, 11, dtype)
+    ref = orpod.rpod_stable(Sr.double().numpy().T, r, sketch_for(11, n, r + p, dtype), 1)
+    assert all(np.isfinite(x).all() for x in gpu)
+    compare(gpu, ref[:3], dtype, r, ref[3]["ritz"])
