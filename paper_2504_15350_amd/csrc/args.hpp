@@ -106,6 +106,14 @@ struct FrobArgs {  // ||S||_F^2: per-workgroup partial sums, then their sum
     int nwg, call;
 };
 
+struct CholArgs {  // Cholesky + inverse of a Gram matrix (R64 null: none)
+    double* R64;
+    float* R32;
+    int* flags;  // status words of the matrix
+    int l, mode;
+};
+constexpr int FLAG_ARRIVED = 63;  // status word: workgroups of a reduction that are done (0 between launches)
+
 struct GramArgs {  // G = Y^T Y, FP64
     const void* Y;
     int64_t ld, M;
@@ -114,16 +122,7 @@ struct GramArgs {  // G = Y^T Y, FP64
     const int* cond;
     int cond_mask;
     int nwg;
-};
-
-struct CholArgs {  // Cholesky + inverse
-    const double* G;
-    int64_t M;
-    double* R64;
-    float* R32;
-    int* flags;
-    int* local;
-    int l, lp, mode;
+    CholArgs chol;
 };
 
 struct JacobiArgs {  // left singular vectors of the small T: from its Gram matrix, or from a factor C

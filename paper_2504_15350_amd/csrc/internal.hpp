@@ -127,26 +127,24 @@ hipError_t launch_center_z(const GroupLaunch<CenterZArgs>& L, hipStream_t st);
 // L: gram_tiles(nt, nwg) workgroups per matrix (nwg = gram_nwg(M, cap, nt),
 // at most one per 64 rows and at most cap; cap 0: about 512 workgroups over
 // the pair groups); R: the reduction, gram_reduce_tiles(nt) workgroups per
-// matrix.
+// matrix. With chol.R64 set, the workgroup that ends last also does the
+// Cholesky factorisation G = R^T R (upper R) and its inverse, FP64:
+//   chol.l: live size; padding becomes identity.
+//   On a non-positive pivot the factorisation is retried on G + s I with
+//   the shift s = 11 (M l + l (l+1)) 2^-53 trace(G) (Fukaya et al., SISC
+//   2020); status words 0 and 1 (the orthonormalisation's own) get
+//   DEV_FLAG_SHIFTED. A failure of the retry sets DEV_FLAG_BREAKDOWN;
+//   non-finite G sets DEV_FLAG_NONFINITE (word 0).
+//   chol.R64 / R32: R^-1, 16 nt x 16 nt column-major.
+//   chol.mode 0: first factorisation of an orthonormalisation (resets word 1);
+//   1: unconditional; 2: run only if word 1 has DEV_FLAG_SHIFTED.
+// Word FLAG_ARRIVED counts the workgroups; it is 0 before and after.
 int64_t gram_partial_count(int nt);
 int gram_nwg(int64_t M, int cap, int nt);
 int gram_tiles(int nt, int nwg);
 int gram_reduce_tiles(int nt);
 hipError_t launch_gram(int tin, int nt, const GroupLaunch<GramArgs>& L, const GroupLaunch<GramArgs>& R,
                        hipStream_t st);
-
-// Cholesky G = R^T R (upper R) and its inverse, one workgroup per matrix, FP64.
-//   l: live size, lp: padded size (<= 128); padding becomes identity.
-//   On a non-positive pivot the factorisation is retried on G + s I with
-//   the shift s = 11 (M l + l (l+1)) 2^-53 trace(G) (Fukaya et al., SISC
-//   2020); *local and *flags get DEV_FLAG_SHIFTED. A failure of the retry
-//   sets DEV_FLAG_BREAKDOWN; non-finite G sets DEV_FLAG_NONFINITE.
-//   R64 / R32: R^-1, lp x lp column-major.
-//   mode 0: first factorisation of an orthonormalisation (resets *local);
-//   mode 1: unconditional; mode 2: run only if *local has DEV_FLAG_SHIFTED.
-//   lp: the padded size shared by the launch's matrices (a multiple of 16;
-//   lp / 16 waves per matrix, blocked).
-hipError_t launch_chol_inv(int lp, const GroupLaunch<CholArgs>& L, hipStream_t st);
 
 // Symmetric eigen-decomposition of the lp x lp FP64 Gram matrix G_B = B B^T
 // (lp a multiple of 16, <= 128): diagonally pivoted Cholesky G_B = P L L^T P^T,

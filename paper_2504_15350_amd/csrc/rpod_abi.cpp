@@ -237,13 +237,13 @@ Layout make_layout(const rpod_desc* d, int64_t wg_target, int gram_cap) {
 // ---------------------------------------------------------------------------
 // Recorded program
 // ---------------------------------------------------------------------------
-enum Kind { K_ZERO, K_OMEGA, K_SX, K_SXE6, K_SX16, K_STQ, K_STQE6, K_STQ16, K_REDUCE, K_GRAM, K_CHOL, K_JACOBI, K_LIFT,
+enum Kind { K_ZERO, K_OMEGA, K_SX, K_SXE6, K_SX16, K_STQ, K_STQE6, K_STQ16, K_REDUCE, K_GRAM, K_JACOBI, K_LIFT,
             K_SIGNS, K_FIN, K_SPLIT, K_WFWD, K_WZ, K_SXW, K_MRES, K_CPREP, K_CY, K_CCROSS, K_CSUM, K_CZ, K_FROB,
             K_EYE, K_ADEC, K_ARANK };
 
 struct Step {
     Kind kind;
-    int tin = 0, tout = 0, nt = 0, lp = 0;  // lp: padded size (small SVD, Cholesky)
+    int tin = 0, tout = 0, nt = 0, lp = 0;  // lp: padded size (small SVD)
     bool vec = true, upper = false, lo = false;
     bool energy = false;  // K_SXE6: also the per-tile sums of squares; K_FROB: only the final sum
     bool tall = false;    // K_SXE6: a product with few columns of S (early loads)
@@ -286,7 +286,8 @@ struct Builder {
     }
 };
 
-constexpr int FLAG_INTS = 64;  // status words per matrix (0: status, 1: orthonormalisation-local)
+constexpr int FLAG_INTS = 64;  // status words per matrix (0: status, 1: orthonormalisation-local, FLAG_ARRIVED)
+static_assert(FLAG_ARRIVED < FLAG_INTS, "one of a matrix's words");
 
 }  // namespace
 
@@ -591,22 +592,18 @@ struct Recorder {
               tiles([](const Item& it) { return (int)((it.L.nP * it.L.lp + 255) / 256); }));
         out.push_back(z);
     }
-    void gram(int dt, std::vector<GramArgs> args) {
+    // the Gram matrix, and with chol its Cholesky factor's inverse
+    void gram(int dt, std::vector<GramArgs> args, const std::vector<CholArgs>& chol = {}) {
         Step s{K_GRAM};
         s.tin = dt; s.nt = L0().nt;
         std::vector<int> t1, t2;
+        for (size_t i = 0; i < chol.size(); ++i) args[i].chol = chol[i];
         for (const GramArgs& a : args) {
             t1.push_back(gram_tiles(s.nt, a.nwg));
             t2.push_back(gram_reduce_tiles(s.nt));
         }
         B.add(s, args, t1);
         B.add(s, args, t2, true);
-        out.push_back(s);
-    }
-    void chol(std::vector<CholArgs> args) {
-        Step s{K_CHOL};
-        s.lp = L0().lp;
-        B.add(s, args, std::vector<int>(args.size(), 1));
         out.push_back(s);
     }
     // CholeskyQR2 of the tall In (ld, M rows, type dt) into Out; the final
@@ -627,8 +624,8 @@ struct Recorder {
         };
         auto cargs = [&](int k, int mode) {
             return each([&](const Item& it) {
-                return CholArgs{P->at<double>(it, it.L.o_G), it.d.m, P->at<double>(it, it.L.o_R64[k]),
-                                P->at<float>(it, it.L.o_R32[k]), P->flags(it), P->flag(it, 1), it.L.l, it.L.lp, mode};
+                return CholArgs{P->at<double>(it, it.L.o_R64[k]), P->at<float>(it, it.L.o_R32[k]), P->flags(it),
+                                it.L.l, mode};
             });
         };
         auto apply = [&](auto src, auto dst, int k, bool cond) {
@@ -637,14 +634,11 @@ struct Recorder {
                               cond ? P->flag(it, 1) : nullptr, cond ? 1 : 0, -1};
             });
         };
-        gram(dt, gargs(In, false));
-        chol(cargs(0, 0));
+        gram(dt, gargs(In, false), cargs(0, 0));
         sx_tall(dt, L0().nt, true, apply(In, Out, 0, false));
-        gram(dt, gargs(Out, false));
-        chol(cargs(kfin, 1));
+        gram(dt, gargs(Out, false), cargs(kfin, 1));
         sx_tall(dt, L0().nt, true, apply(Out, Out, kfin, true));  // shifted retry, in place (no-op otherwise)
-        gram(dt, gargs(Out, true));
-        chol(cargs(kfin, 2));
+        gram(dt, gargs(Out, true), cargs(kfin, 2));
         split_q();
     }
     // One CholeskyQR of the tall Y into Q1 = Y R^-1 for an iterate of which only
@@ -669,8 +663,8 @@ struct Recorder {
         };
         auto cargs = [&](int k, int mode) {
             return each([&](const Item& it) {
-                return CholArgs{P->at<double>(it, it.L.o_G), it.d.m, P->at<double>(it, it.L.o_R64[k]),
-                                P->at<float>(it, it.L.o_R32[k]), P->flags(it), P->flag(it, 1), it.L.l, it.L.lp, mode};
+                return CholArgs{P->at<double>(it, it.L.o_R64[k]), P->at<float>(it, it.L.o_R32[k]), P->flags(it),
+                                it.L.l, mode};
             });
         };
         auto apply = [&](auto src, auto dst, int k, bool cond) {
@@ -679,11 +673,9 @@ struct Recorder {
                               cond ? P->flag(it, 1) : nullptr, cond ? 1 : 0, -1};
             });
         };
-        gram(dt, gargs(In, false));
-        chol(cargs(0, 0));
+        gram(dt, gargs(In, false), cargs(0, 0));
         sx_tall(dt, L0().nt, true, apply(In, Out, 0, false));
-        gram(dt, gargs(Out, true));                              // after a shift only
-        chol(cargs(2, 2));
+        gram(dt, gargs(Out, true), cargs(2, 2));                              // after a shift only
         sx_tall(dt, L0().nt, true, apply(Out, Out, 2, true));    // in place, after a shift only
         split_q();
     }
@@ -721,8 +713,8 @@ struct Recorder {
         };
         auto cargs = [&](int k, int mode) {
             return each([&](const Item& it) {
-                return CholArgs{P->at<double>(it, it.L.o_G), it.d.m, P->at<double>(it, it.L.o_R64[k]),
-                                P->at<float>(it, it.L.o_R32[k]), P->flags(it), P->flag(it, 1), it.L.l, it.L.lp, mode};
+                return CholArgs{P->at<double>(it, it.L.o_R64[k]), P->at<float>(it, it.L.o_R32[k]), P->flags(it),
+                                it.L.l, mode};
             });
         };
         auto apply = [&](int k, bool cond) {
@@ -731,14 +723,11 @@ struct Recorder {
                               cond ? P->flag(it, 1) : nullptr, cond ? 1 : 0, -1};
             });
         };
-        gram(dt, gargs(false));
-        chol(cargs(0, 0));
+        gram(dt, gargs(false), cargs(0, 0));
         sx_tall(dt, L0().nt, true, apply(0, false));
-        gram(dt, gargs(false));
-        chol(cargs(1, 1));
+        gram(dt, gargs(false), cargs(1, 1));
         sx_tall(dt, L0().nt, true, apply(1, true));   // shifted retry only
-        gram(dt, gargs(true));
-        chol(cargs(1, 2));
+        gram(dt, gargs(true), cargs(1, 2));
         sx_tall(dt, L0().nt, true, apply(1, false));  // the last factor
     }
     // *dst = ||Zt[:, :l]||_F^2 (FP64, n rows): adaptive plans, ||B_i||_F^2 of a block
@@ -805,16 +794,14 @@ struct Recorder {
         };
         auto cargs = [&](int k, int mode) {
             return each([&](const Item& it) {
-                return CholArgs{P->at<double>(it, it.L.o_G), it.d.n, P->at<double>(it, it.L.o_R64[k]),
-                                P->at<float>(it, it.L.o_R32[k]), P->flags(it), P->flag(it, 1), it.L.l, it.L.lp, mode};
+                return CholArgs{P->at<double>(it, it.L.o_R64[k]), P->at<float>(it, it.L.o_R32[k]), P->flags(it),
+                                it.L.l, mode};
             });
         };
-        gram(DT_F64, gargs(false, false));
-        chol(cargs(0, 0));
+        gram(DT_F64, gargs(false, false), cargs(0, 0));
         sx(DT_F64, tin, L0().nt, true, app(&Layout::o_Zw, &Layout::o_X, 0, false));
         sx(DT_F64, DT_F64, L0().nt, true, app(&Layout::o_Zw, &Layout::o_Zw2, 0, true));
-        gram(DT_F64, gargs(true, true));
-        chol(cargs(2, 2));
+        gram(DT_F64, gargs(true, true), cargs(2, 2));
         sx(DT_F64, tin, L0().nt, true, app(&Layout::o_Zw2, &Layout::o_X, 2, true));
     }
     // Orthonormal Q2 of the n x l iterate Zw = T^T by CholeskyQR2 (shifted
@@ -837,18 +824,15 @@ struct Recorder {
         };
         auto cargs = [&](int k, int mode) {
             return each([&](const Item& it) {
-                return CholArgs{P->at<double>(it, it.L.o_G), it.d.n, P->at<double>(it, it.L.o_R64[k]),
-                                P->at<float>(it, it.L.o_R32[k]), P->flags(it), P->flag(it, 1), it.L.l, it.L.lp, mode};
+                return CholArgs{P->at<double>(it, it.L.o_R64[k]), P->at<float>(it, it.L.o_R32[k]), P->flags(it),
+                                it.L.l, mode};
             });
         };
-        gram(DT_F64, gargs(&Layout::o_Zw, false));
-        chol(cargs(0, 0));
+        gram(DT_F64, gargs(&Layout::o_Zw, false), cargs(0, 0));
         sx(DT_F64, DT_F64, L0().nt, true, app(&Layout::o_Zw, 0, false));
-        gram(DT_F64, gargs(&Layout::o_Zw2, false));
-        chol(cargs(2, 1));
+        gram(DT_F64, gargs(&Layout::o_Zw2, false), cargs(2, 1));
         sx(DT_F64, DT_F64, L0().nt, true, app(&Layout::o_Zw2, 2, true));  // shifted retry, in place
-        gram(DT_F64, gargs(&Layout::o_Zw2, true));
-        chol(cargs(2, 2));
+        gram(DT_F64, gargs(&Layout::o_Zw2, true), cargs(2, 2));
         sx(DT_F64, DT_F64, L0().nt, true, app(&Layout::o_Zw2, 2, false));  // Q2, in place
     }
     void finish() {
@@ -1089,7 +1073,6 @@ hipError_t run_step(const rpod_plan_s* P, const Step& s, hipStream_t st) {
         case K_STQ16: return launch_stq16(s.tin, s.nt, s.lo, s.vec, P->gl<StqArgs>(s, false), st);
         case K_REDUCE: return launch_reduce_slabs(P->gl<ReduceArgs>(s, false), st);
         case K_GRAM: return launch_gram(s.tin, s.nt, P->gl<GramArgs>(s, false), P->gl<GramArgs>(s, true), st);
-        case K_CHOL: return launch_chol_inv(s.lp, P->gl<CholArgs>(s, false), st);
         case K_JACOBI: return launch_jacobi(s.lp, P->gl<JacobiArgs>(s, false), st);
         case K_LIFT: return launch_lift_coef(P->gl<LiftArgs>(s, false), st);
         case K_SPLIT: return launch_split16(s.tin, P->gl<SplitArgs>(s, false), st);

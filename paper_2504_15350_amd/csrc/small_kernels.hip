@@ -2,7 +2,7 @@
 //
 //   k_omega        Gaussian sketch (Alg. 1 step 1) from Philox4x32-10
 //   k_gram         FP64 Gram matrix Y^T Y of a tall matrix on FP64 MFMA
-//   k_chol_blk     Cholesky + triangular inverse for CholeskyQR (step 4)
+//   k_gram_reduce  its partial sums, then Cholesky + triangular inverse for CholeskyQR (step 4)
 //   k_jacobi       SVD of the small T of step 6 via the eigenvectors of T T^T
 //                  (pivoted Cholesky, then preconditioned one-sided Jacobi)
 //   k_lift_coef    the small factors of the lift (step 7) and the coefficients
@@ -264,92 +264,6 @@ __global__ __launch_bounds__(256) void k_gram(Group<GramArgs> g) {
     }
 }
 
-// grouped: npairs(nt) tiles of 256 elements per matrix
-__global__ __launch_bounds__(256) void k_gram_reduce(Group<GramArgs> g, int nt) {
-    if (group_skipped(g)) return;
-    __shared__ double part[8][32];
-    const int it = group_item(g.tstart, g.count, blockIdx.x);
-    const GramArgs& ga = g.args[it];
-    if (ga.cond != nullptr && !(*ga.cond & ga.cond_mask)) return;
-    const int np = nt * (nt + 1) / 2;
-    // 32 entries per workgroup, eight threads per entry: thread t sums the
-    // partials w = t, t + 8, .. (independent loads in flight), and the eight
-    // sums are combined in a fixed order
-    const int el = threadIdx.x & 31, t = threadIdx.x >> 5;
-    const int e = (blockIdx.x - g.tstart[it]) * 32 + el;
-    const bool live = e < np * 256;
-    double acc = 0.0;
-    if (live) {
-        const GLOBAL double* src = gbl(ga.Gpart) + e;  // entry e = pair e / 256, element e mod 256
-        const int64_t wstride = (int64_t)np * 256;
-        const int nwg = ga.nwg;
-        double a4[4] = {0, 0, 0, 0};
-        int w = t;
-        for (; w + 24 < nwg; w += 32)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) a4[u] += src[(int64_t)(w + 8 * u) * wstride];
-        for (; w < nwg; w += 8) a4[0] += src[(int64_t)w * wstride];
-        acc = (a4[0] + a4[1]) + (a4[2] + a4[3]);
-    }
-    part[t][el] = acc;
-    __syncthreads();
-    if (t != 0 || !live) return;
-    const double s = ((part[0][el] + part[1][el]) + (part[2][el] + part[3][el])) +
-                     ((part[4][el] + part[5][el]) + (part[6][el] + part[7][el]));
-    const int p = e / 256, mm = (e % 256) / 16, nn = e % 16;
-    int a = 0, q = p;
-    while (q >= nt - a) { q -= nt - a; ++a; }
-    const int b = a + q;
-    const int lp = 16 * nt;
-    GLOBAL double* G = gbl(ga.G);
-    G[(16 * a + mm) * lp + 16 * b + nn] = s;
-    G[(16 * b + nn) * lp + 16 * a + mm] = s;
-}
-
-// Partial workgroups per pair group: one per 4 row blocks, at most `cap`;
-// by default (cap 0) 256 for a single pair group (measured: more partials
-// cost more in the reduction than they save) and about 512 workgroups over
-// several pair groups (two waves per SIMD), rounded down to a multiple of 8.
-int gram_nwg(int64_t M, int cap, int nt) {
-    const int64_t nrb = (M + 15) / 16;
-    int64_t nwg = (nrb + 3) / 4;
-    if (cap < 1 || cap > GRAM_WGS) cap = gram_groups(nt) == 1 ? 256 : (GRAM_WGS / gram_groups(nt)) & ~7;
-    if (nwg > cap) nwg = cap;
-    if (nwg < 1) nwg = 1;
-    return (int)nwg;
-}
-
-int gram_tiles(int nt, int nwg) { return nwg * gram_groups(nt); }
-int gram_reduce_tiles(int nt) { return npairs_of(nt) * 8; }  // 32 entries per workgroup
-
-template <typename Tin, int NT>
-static hipError_t gram_nt(const GroupLaunch<GramArgs>& L, const GroupLaunch<GramArgs>& R, hipStream_t st) {
-    hipLaunchKernelGGL((k_gram<Tin, NT>), dim3(L.tiles), dim3(256), 0, st, mkg(L));
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gram_reduce, dim3(R.tiles), dim3(256), 0, st, mkg(R), NT);
-    return hipGetLastError();
-}
-
-template <typename Tin>
-static hipError_t gram_dispatch(int nt, const GroupLaunch<GramArgs>& L, const GroupLaunch<GramArgs>& R,
-                                hipStream_t st) {
-    switch (nt) {
-#define RPOD_GRAM_CASE(K) case K: return gram_nt<Tin, K>(L, R, st);
-        RPOD_GRAM_CASE(1) RPOD_GRAM_CASE(2) RPOD_GRAM_CASE(3) RPOD_GRAM_CASE(4)
-        RPOD_GRAM_CASE(5) RPOD_GRAM_CASE(6) RPOD_GRAM_CASE(7) RPOD_GRAM_CASE(8)
-#undef RPOD_GRAM_CASE
-        default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_gram(int tin, int nt, const GroupLaunch<GramArgs>& L, const GroupLaunch<GramArgs>& R,
-                       hipStream_t st) {
-    if (tin == DT_F64) return gram_dispatch<double>(nt, L, R, st);
-    if (tin == DT_F32) return gram_dispatch<float>(nt, L, R, st);
-    return hipErrorInvalidValue;
-}
-
 // 1 / sqrt(x) and 1 / x for x > 0 (finite): the hardware estimates refined by
 // two Newton steps each (the error of the estimate squares at every step).
 __device__ __forceinline__ double rsqrt_nr(double x) {
@@ -375,254 +289,403 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
 }
 
 // ---------------------------------------------------------------------------
-// Blocked version for lp = 16 NB <= 128 with NB waves: lane j of wave p
-// keeps rows 16 p .. 16 p + 15 of columns j and j + 64 (lp > 64) in
-// registers. Step k: wave k / 16 reads the pivot from the lane holding
-// column k, scales its row k into R[k][:] (1 / sqrt from the refined
-// estimate) and updates its rows below k, A[i][j] -= R[k][i] R[k][j]
-// (right-looking), the multipliers R[k][i] read from the lanes holding them;
-// after its 16 rows the wave publishes them through LDS and, after one
-// barrier per 16 steps, the waves below apply the 16 updates to their rows.
-// (Factorisation 45 us at lp = 128 and 36 us at lp = 96, against 55 and 48 us
-// with one barrier per step; bit-identical results.)
-// The inverse X = R^-1 is formed by 16 x 16 blocks: the diagonal blocks by
-// forward substitution on rows (lane t: x[c] = (delta_tc - sum_{k<c} x[k]
-// R[k][c]) / R[c][c]), then the blocks at distance d = 1, 2, .. above the
-// diagonal, X_ij = -X_ii sum_{k=i+1..j} R_ik X_kj, one wave per block. R and
-// X are kept in LDS as their upper-triangular 16 x 16 blocks only (block
-// (ib, jb), ib <= jb, at jb (jb + 1) / 2 + ib, column-major inside).
+// Cholesky G = R^T R and X = R^-1 for lp = 16 NB <= 128, by the workgroup that
+// finishes the reduction of G. Wave w keeps the blocks (i, w), i <= w, of the
+// 16 x 16 blocks of A as FP64 MFMA accumulators (right-looking; lane (n, kg)
+// holds rows kg + 4 v of column n). A 16 x 16 block stored row-major is then
+// both operands of the next update as it stands: A_iw -= R_pi^T R_pw takes row
+// 4 s + kg of either block in MFMA step s. gfx950's FP64 MFMA is a chain of
+// fused multiply-adds in the order of k, so every entry sees the updates of a
+// step-by-step elimination, in its order.
+//   Panel row p is factorised by one wave per 64 columns: lane j holds the 16
+// entries of column j, and next to them a copy of the diagonal block's column
+// j mod 16, so that the multipliers R[k][16 p + r] are broadcast over each row
+// of 16 lanes by the multiply-add itself. The other waves meanwhile apply the
+// previous panel to their blocks below the next panel row.
+//   X: the diagonal blocks by forward substitution on rows (lane t: x[c] =
+// (delta_tc - sum_{k<c} x[k] R[k][c]) / R[c][c]), then wave j goes up its block
+// column, X_ij = -X_ii sum_{k=i+1..j} R_ik X_kj, the X_kj in registers as they
+// come out of the matrix cores. Rows are padded to 17 entries, so that the
+// transposed operand reads of that product meet no bank twice.
+//   Bound by the serial chain of one workgroup (instruction issue of one wave
+// per SIMD in the panels). Measured at lp = 32 / 64 / 96 / 128, a whole launch
+// with the reduction of one partial: 10.4 / 18.9 / 30.8 / 44 us, against 15.4 /
+// 28.2 / 55.5 / 76 us for the factorisation alone in a kernel of its own (rows
+// of 16 in the registers of a wave, multipliers by readlane and LDS broadcast);
+// the same bits.
 // Padding rows and columns of R become identity, so X has identity padding.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int blk(int ib, int jb) { return (jb * (jb + 1) / 2 + ib) * 256; }  // ib <= jb
+constexpr int CHOL_LD = 17, CHOL_BLK = 16 * CHOL_LD;
+__device__ __forceinline__ int blk(int ib, int jb) { return (jb * (jb + 1) / 2 + ib) * CHOL_BLK; }  // ib <= jb
+
+// v of lane K of each row of 16 lanes
+template <int K> __device__ __forceinline__ double row_bcast(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, 0x150 + K, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), 0x150 + K, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// a[r] -= x(lane r of the row) m, b[r] -= x(lane r of the row) n for R <= r < R + N (a DPP operand needs two
+// wait states after a VALU write: inside)
+template <int R, int N> __device__ __forceinline__ void fms_bcast(double* a, double* b, double x, double m, double n) {
+#define RPOD_FMS(A, M, K) "v_fmac_f64_dpp " A ", -%[x], " M " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n"
+    if constexpr (N >= 4) {
+        asm volatile("s_nop 1\n" RPOD_FMS("%0", "%[m]", "%[k0]") RPOD_FMS("%4", "%[n]", "%[k0]")
+                     RPOD_FMS("%1", "%[m]", "%[k1]") RPOD_FMS("%5", "%[n]", "%[k1]")
+                     RPOD_FMS("%2", "%[m]", "%[k2]") RPOD_FMS("%6", "%[n]", "%[k2]")
+                     RPOD_FMS("%3", "%[m]", "%[k3]") RPOD_FMS("%7", "%[n]", "%[k3]")
+                     : "+v"(a[R]), "+v"(a[R + 1]), "+v"(a[R + 2]), "+v"(a[R + 3]), "+v"(b[R]), "+v"(b[R + 1]),
+                       "+v"(b[R + 2]), "+v"(b[R + 3])
+                     : [x] "v"(x), [m] "v"(m), [n] "v"(n), [k0] "n"(R), [k1] "n"(R + 1), [k2] "n"(R + 2),
+                       [k3] "n"(R + 3));
+        fms_bcast<R + 4, N - 4>(a, b, x, m, n);
+    } else if constexpr (N > 0) {
+        asm volatile("s_nop 1\n" RPOD_FMS("%0", "%[m]", "%[k0]") RPOD_FMS("%1", "%[n]", "%[k0]")
+                     : "+v"(a[R]), "+v"(b[R])
+                     : [x] "v"(x), [m] "v"(m), [n] "v"(n), [k0] "n"(R));
+        fms_bcast<R + 1, N - 1>(a, b, x, m, n);
+    }
+#undef RPOD_FMS
+}
+// s[c] -= r[c](lane K of the row) x for C <= c < C + N
+template <int K, int C, int N> __device__ __forceinline__ void fms_from(double* s, const double* r, double x) {
+#define RPOD_FMS(A, B) "v_fmac_f64_dpp " A ", -" B ", %[x] row_newbcast:%[k] row_mask:0xf bank_mask:0xf\n"
+    if constexpr (N >= 4) {
+        asm volatile("s_nop 1\n" RPOD_FMS("%0", "%[r0]") RPOD_FMS("%1", "%[r1]") RPOD_FMS("%2", "%[r2]")
+                     RPOD_FMS("%3", "%[r3]")
+                     : "+v"(s[C]), "+v"(s[C + 1]), "+v"(s[C + 2]), "+v"(s[C + 3])
+                     : [x] "v"(x), [r0] "v"(r[C]), [r1] "v"(r[C + 1]), [r2] "v"(r[C + 2]), [r3] "v"(r[C + 3]), [k] "n"(K));
+        fms_from<K, C + 4, N - 4>(s, r, x);
+    } else if constexpr (N > 0) {
+        asm volatile("s_nop 1\n" RPOD_FMS("%0", "%[r0]") : "+v"(s[C]) : [x] "v"(x), [r0] "v"(r[C]), [k] "n"(K));
+        fms_from<K, C + 1, N - 1>(s, r, x);
+    }
+#undef RPOD_FMS
+}
+template <int I, int N, typename F> __device__ __forceinline__ void unroll(F f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        unroll<I + 1, N>(f);
+    }
+}
+
+struct CholShared {
+    double* R;   // upper blocks of R, then R^-1's diagonal blocks in X
+    double* X;
+    double* gd;  // diagonal of G
+    int* fail;
+};
 
 template <int NB>
-__global__ __launch_bounds__(64 * NB) void k_chol_blk(Group<CholArgs> gr) {
-    if (group_skipped(gr)) return;
-    constexpr int LP = 16 * NB, NTHR = 64 * NB, CPL = (LP + 63) / 64, NTRI = NB * (NB + 1) / 2 * 256;
-    __shared__ __attribute__((aligned(16))) double Rs[NTRI];  // R, upper blocks
-    __shared__ __attribute__((aligned(16))) double Xs[NTRI];  // R^-1, upper blocks
-    __shared__ int s_fail;
-    const CholArgs& a = gr.args[blockIdx.x];  // one workgroup per matrix
-    const int tid = threadIdx.x, j = tid & 63, wave = tid >> 6;
-    const int l = a.l, lp = a.lp;
-    const double* __restrict__ G = a.G;
-    if (a.mode == 2 && !(*a.local & DEV_FLAG_SHIFTED)) return;
-    if (a.mode == 0 && tid == 0) *a.local = 0;
+__device__ __forceinline__ void chol_body(const GramArgs& a, const CholShared& sh) {
+    constexpr int LP = 16 * NB, PW = (NB + 3) / 4;  // PW: panel waves
+    double *Rs = sh.R, *Xs = sh.X, *gd = sh.gd;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 15, kg = lane >> 4;  // MFMA lane; kg is also the lane's row of 16 lanes
+    const CholArgs& c = a.chol;
+    const int l = c.l, mode = c.mode;
+    int* local = c.flags + 1;
+    const GLOBAL double* G = gbl(a.G);
+    if (mode == 2 && !(*local & DEV_FLAG_SHIFTED)) return;  // uniform
+    if (mode == 0 && tid == 0) *local = 0;
 
-    double w[CPL][16];  // A[16 wave + r][j + 64 cc]
-    double gd[CPL];
+    f64x4 w[NB];  // A[16 i + kg + 4 v][16 wave + n], then X
     bool fin = true;
+    auto load = [&](bool first, double shift) {
 #pragma unroll
-    for (int cc = 0; cc < CPL; ++cc) {
-        const int col = j + 64 * cc;
+        for (int i = 0; i < NB; ++i)
+            if (wave < NB && i <= wave) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            w[cc][r] = col < LP ? G[(16 * wave + r) * lp + col] : 0.0;
-            fin = fin && isfinite(w[cc][r]);
-        }
-        gd[cc] = col < LP ? G[col * lp + col] : 0.0;
-    }
+                for (int v = 0; v < 4; ++v) w[i][v] = G[(16 * i + kg + 4 * v) * LP + 16 * wave + n];
+            }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (wave < NB && i <= wave) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) fin = fin && isfinite(w[i][v]);
+                if (i == wave) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (kg + 4 * v == n) {
+                            if (first) gd[16 * wave + n] = w[i][v];
+                            w[i][v] += shift;
+                        }
+                }
+                if (16 * wave + 16 > l) {  // padding (i <= wave: its rows are in the same block column)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int row = 16 * i + kg + 4 * v, col = 16 * wave + n;
+                        if (row >= l || col >= l) w[i][v] = row == col ? 1.0 : 0.0;
+                    }
+                }
+            }
+    };
+    load(true, 0.0);
     bool ok = __syncthreads_and(fin) != 0;
-    if (!ok && tid == 0) atomicOr(a.flags, DEV_FLAG_NONFINITE);
+    if (!ok && tid == 0) atomicOr(c.flags, DEV_FLAG_NONFINITE);
     if (ok) {
 #pragma unroll 1
         for (int attempt = 0; attempt < 2; ++attempt) {
             if (attempt == 1) {
                 double tr = 0.0;
-                for (int k = 0; k < l; ++k) tr += G[k * lp + k];
-                const double shift = 11.0 * ((double)a.M * l + (double)l * (l + 1)) * 0x1.0p-53 * tr;
-#pragma unroll
-                for (int cc = 0; cc < CPL; ++cc) {
-                    const int col = j + 64 * cc;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        w[cc][r] = (col < LP ? G[(16 * wave + r) * lp + col] : 0.0) +
-                                   (16 * wave + r == col ? shift : 0.0);
-                }
+                for (int k = 0; k < l; ++k) tr += gd[k];
+                load(false, 11.0 * ((double)a.M * l + (double)l * (l + 1)) * 0x1.0p-53 * tr);
             }
-            if (tid == 0) s_fail = 0;
+            if (tid == 0) *sh.fail = 0;
+            // a panel row to be factorised: its diagonal block apart (both panel waves read it), the
+            // others where R goes
+            auto put = [&](int i, const f64x4& x) {
+                double* d = (i == wave ? Xs + i * CHOL_BLK : Rs + blk(i, wave)) + kg * CHOL_LD + n;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) d[4 * v * CHOL_LD] = x[v];
+            };
+            // w[i] -= R_pi^T R_p,wave
+            auto update = [&](int i, int p, const double (&rb)[4], f64x4& x) {
+                const double* ra = Rs + blk(p, i) + kg * CHOL_LD + n;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) x = mfma_16x16x4(-ra[4 * s * CHOL_LD], rb[s], x);
+            };
+            auto row_of = [&](int p, double (&rb)[4]) {
+                const double* r = Rs + blk(p, wave) + kg * CHOL_LD + n;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) rb[s] = r[4 * s * CHOL_LD];
+            };
+            if (wave < NB) put(0, w[0]);
             __syncthreads();
-            bool fail = false;
-            // Panel pb (rows and columns 16 pb .. 16 pb + 15): wave pb factorises its own 16 rows
-            // without barriers (the multipliers R[k][16 pb + r] come from the lanes holding those
-            // columns), publishes them through LDS (alternately in Xs and Rs, which hold R and its
-            // inverse only afterwards), and after one barrier every wave below applies the panel's
-            // 16 rank-1 updates to its rows, in the order of k as a step-by-step update would.
-            for (int pb = 0; pb < NB; ++pb) {
-                if (16 * pb >= l) break;
-                double* rp = (pb & 1) ? Rs : Xs;  // R[16 pb + kk][col] at rp[kk * LP + col]
-                if (wave == pb) {
+#pragma unroll 1
+            for (int p = 0; p < NB; ++p) {
+                if (wave < PW && 4 * wave + 3 >= p) {
+                    const int cb = 4 * wave + kg;  // this row of lanes' block column
+                    const bool live = cb >= p && cb < NB;
+                    const double* dsrc = Xs + p * CHOL_BLK + n;
+                    double* xdst = Rs + blk(p, live ? cb : p) + n;
+                    const double* xsrc = cb > p && live ? xdst : dsrc;
+                    double d[16], x[16];
 #pragma unroll
-                    for (int kk = 0; kk < 16; ++kk) {
-                        const int k = 16 * pb + kk;
-                        if (k >= l) continue;  // uniform; no break, so the loop unrolls
-                        const bool khi = CPL > 1 && k >= 64;
-                        const double d = read_lane(khi ? w[CPL - 1][kk] : w[0][kk], k & 63);
-                        const double tol = (double)l * 0x1.0p-52 * read_lane(khi ? gd[CPL - 1] : gd[0], k & 63);
-                        if (!(d > tol) || !(d > 0.0)) {  // non-positive, tiny or NaN pivot
-                            // recorded once; the row becomes NaN, so every later pivot fails too
-                            if (j == 0) s_fail = 1;
-#pragma unroll
-                            for (int cc = 0; cc < CPL; ++cc) w[cc][kk] = __builtin_nan("");
-                        } else {
-                            const double rinv = rsqrt_nr(d);
-#pragma unroll
-                            for (int cc = 0; cc < CPL; ++cc) {
-                                const int col = j + 64 * cc;
-                                w[cc][kk] = (col >= k) ? w[cc][kk] * rinv : 0.0;  // R[k][col]
-                            }
-                        }
-#pragma unroll
-                        for (int r = kk + 1; r < 16; ++r) {  // the panel's rows below row k
-                            const int cr = 16 * pb + r;
-                            const bool rhi = CPL > 1 && cr >= 64;
-                            const double rk = read_lane(rhi ? w[CPL - 1][kk] : w[0][kk], cr & 63);  // R[k][cr]
-#pragma unroll
-                            for (int cc = 0; cc < CPL; ++cc) w[cc][r] -= rk * w[cc][kk];
-                        }
+                    for (int r = 0; r < 16; ++r) {
+                        d[r] = dsrc[r * CHOL_LD];
+                        x[r] = xsrc[r * CHOL_LD];
                     }
+                    double piv = 0.0;  // lane n of a row: pivot 16 p + n
+                    unroll<0, 16>([&](auto KK) {
+                        constexpr int kk = KK;
+                        piv = n == kk ? d[kk] : piv;
+                        const double rinv = rsqrt_nr(row_bcast<kk>(d[kk]));
+                        d[kk] *= rinv;  // R[k][:] (left of column k: of no use, never read)
+                        x[kk] *= rinv;
+                        fms_bcast<kk + 1, 15 - kk>(d, x, d[kk], d[kk], x[kk]);
+                    });
+                    // a non-positive, tiny or NaN pivot (the rows after it are thrown away)
+                    const bool bad = !(piv > (double)l * 0x1.0p-52 * gd[16 * p + n]) || !(piv > 0.0);
+                    if (bad) *sh.fail = 1;
+                    if (live) {
 #pragma unroll
-                    for (int cc = 0; cc < CPL; ++cc) {
-                        const int col = j + 64 * cc;
-                        if (col < LP) {
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) rp[r * LP + col] = w[cc][r];
-                        }
+                        for (int r = 0; r < 16; ++r) xdst[r * CHOL_LD] = x[r];
                     }
                 }
-                __syncthreads();
-                if (wave > pb) {
-                    const int nk = min(16, l - 16 * pb);
-                    for (int kk = 0; kk < nk; ++kk) {
-                        double rkc[CPL];
+                double rb[4];
+                if (p > 0 && wave > p && wave < NB) {  // panel p - 1 on the blocks below panel row p
+                    row_of(p - 1, rb);
 #pragma unroll
-                        for (int cc = 0; cc < CPL; ++cc) {
-                            const int col = j + 64 * cc;
-                            rkc[cc] = col < LP ? rp[kk * LP + col] : 0.0;
-                        }
-                        const double* ra = rp + kk * LP + 16 * wave;  // R[k][16 wave + r], the same in every lane
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const double a = ra[r];
-#pragma unroll
-                            for (int cc = 0; cc < CPL; ++cc) w[cc][r] -= a * rkc[cc];
-                        }
-                    }
+                    for (int i = 2; i < NB; ++i)
+                        if (i > p && i <= wave) update(i, p - 1, rb, w[i]);
                 }
+                __syncthreads();  // panel row p final
+                if (wave > p && wave < NB) {
+                    row_of(p, rb);
+#pragma unroll
+                    for (int i = 1; i < NB; ++i)
+                        if (i == p + 1) {
+                            update(i, p, rb, w[i]);
+                            put(i, w[i]);
+                        }
+                }
+                __syncthreads();  // panel row p + 1 staged
             }
-            __syncthreads();
-            fail = s_fail != 0;
-            __syncthreads();  // every thread has read s_fail
+            const bool fail = *sh.fail != 0;
+            __syncthreads();  // every thread has read it
             if (!fail) break;
             if (attempt == 0) {
                 if (tid == 0) {
-                    atomicOr(a.flags, DEV_FLAG_SHIFTED);
-                    *a.local |= DEV_FLAG_SHIFTED;
+                    atomicOr(c.flags, DEV_FLAG_SHIFTED);
+                    *local |= DEV_FLAG_SHIFTED;
                 }
             } else {
-                if (tid == 0) atomicOr(a.flags, DEV_FLAG_BREAKDOWN);
+                if (tid == 0) atomicOr(c.flags, DEV_FLAG_BREAKDOWN);
                 ok = false;
             }
         }
     }
+    GLOBAL double* R64 = gbl(c.R64);
+    GLOBAL float* R32 = gbl(c.R32);
     if (ok) {
-        // R (upper blocks; lower part of the diagonal blocks zero) with identity padding
-#pragma unroll
-        for (int cc = 0; cc < CPL; ++cc) {
-            const int col = j + 64 * cc, cb = col >> 4;
-            if (col < LP && wave <= cb) {
-                double* dst = Rs + blk(wave, cb) + (col & 15) * 16;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int i = 16 * wave + r;
-                    dst[r] = (i <= col) ? ((i < l && col < l) ? w[cc][r] : (i == col ? 1.0 : 0.0)) : 0.0;
-                }
-            }
-        }
-        __syncthreads();
-        if (j < 16) {  // diagonal block of wave p: lane t = row t
-            const double* Rd = Rs + blk(wave, wave);
-            double x[16];
+        if (wave < PW) {  // diagonal blocks 4 wave + kg, lane n = row n
+            const int b = min(4 * wave + kg, NB - 1);
+            const double* Rd = Rs + blk(b, b) + n * CHOL_LD;
+            double rd[16], s0[16], s1[16];  // rd[c]: R[n][c]; even and odd k of x[c]'s sum, then x[c] in s0
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
-                double s0 = (c == j) ? 1.0 : 0.0, s1 = 0.0;
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    if (k < c) {
-                        const double rkc = Rd[c * 16 + k];
-                        if (k & 1) s1 -= x[k] * rkc;
-                        else s0 -= x[k] * rkc;
-                    }
-                }
-                x[c] = (s0 + s1) * rcp_nr(Rd[c * 16 + c]);
+                rd[c] = Rd[c];
+                s0[c] = c == n ? 1.0 : 0.0;
+                s1[c] = 0.0;
             }
-            double* Xd = Xs + blk(wave, wave);
+            const double rc = rcp_nr(Rd[n]);
+            unroll<0, 16>([&](auto KK) {
+                constexpr int k = KK;
+                s0[k] = (s0[k] + s1[k]) * row_bcast<k>(rc);
+                fms_from<k, k + 1, 15 - k>(k & 1 ? s1 : s0, rd, s0[k]);
+            });
+            double* Xd = Xs + b * CHOL_BLK + n * CHOL_LD;
 #pragma unroll
-            for (int c = 0; c < 16; ++c) Xd[c * 16 + j] = x[c];  // zero below the diagonal
+            for (int c = 0; c < 16; ++c) Xd[c] = s0[c];  // zero below the diagonal
         }
         __syncthreads();
-        const int r = j & 15, cq = j >> 4;  // lane: row r, columns 4 cq .. 4 cq + 3 of a block
-        for (int d = 1; d < NB; ++d) {
-            const int ib = wave, jb = wave + d;
-            if (jb < NB) {
-                double tv[4] = {0.0, 0.0, 0.0, 0.0};  // T = sum_{kb=ib+1..jb} R_{ib,kb} X_{kb,jb}
-                for (int kb = ib + 1; kb <= jb; ++kb) {
-                    const double* Rb = Rs + blk(ib, kb);
-                    const double* Xb = Xs + blk(kb, jb);
+        if (wave < NB) {
 #pragma unroll
-                    for (int m = 0; m < 16; ++m) {
-                        const double rv = Rb[m * 16 + r];
+            for (int i = 0; i < NB; ++i)
+                if (i == wave) {
 #pragma unroll
-                        for (int cc = 0; cc < 4; ++cc) tv[cc] = fma(rv, Xb[(4 * cq + cc) * 16 + m], tv[cc]);
-                    }
+                    for (int v = 0; v < 4; ++v) w[i][v] = Xs[i * CHOL_BLK + (kg + 4 * v) * CHOL_LD + n];
                 }
-                // T goes through the (still unused) slot of X_{ib,jb}: written, read, then overwritten
-                double* T = Xs + blk(ib, jb);
 #pragma unroll
-                for (int cc = 0; cc < 4; ++cc) T[(4 * cq + cc) * 16 + r] = tv[cc];
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                const double* Xd = Xs + blk(ib, ib);
-                double xv[4] = {0.0, 0.0, 0.0, 0.0};  // X_{ib,jb} = -X_{ib,ib} T
+            for (int ib = NB - 2; ib >= 0; --ib)
+                if (ib < wave) {
+                    f64x4 t = {0.0, 0.0, 0.0, 0.0}, x = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int m = 0; m < 16; ++m) {
-                    const double xim = Xd[m * 16 + r];
+                    for (int kb = ib + 1; kb < NB; ++kb)
+                        if (kb <= wave) {
+                            const double* ra = Rs + blk(ib, kb) + n * CHOL_LD + kg;
 #pragma unroll
-                    for (int cc = 0; cc < 4; ++cc) xv[cc] = fma(-xim, T[(4 * cq + cc) * 16 + m], xv[cc]);
+                            for (int s = 0; s < 4; ++s) t = mfma_16x16x4(ra[4 * s], w[kb][s], t);
+                        }
+                    const double* xa = Xs + ib * CHOL_BLK + n * CHOL_LD + kg;
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) x = mfma_16x16x4(-xa[4 * s], t[s], x);
+                    w[ib] = x;
                 }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // column-major
 #pragma unroll
-                for (int cc = 0; cc < 4; ++cc) T[(4 * cq + cc) * 16 + r] = xv[cc];
-            }
-            __syncthreads();
-        }
-        for (int e = tid; e < LP * LP; e += NTHR) {
-            const int t = e % LP, c = e / LP;
-            const double v = ((t >> 4) <= (c >> 4)) ? Xs[blk(t >> 4, c >> 4) + (c & 15) * 16 + (t & 15)] : 0.0;
-            a.R64[e] = v;
-            a.R32[e] = (float)v;
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const double x = i <= wave ? w[i][v] : 0.0;
+                    const int e = (16 * wave + n) * LP + 16 * i + kg + 4 * v;
+                    R64[e] = x;
+                    R32[e] = (float)x;
+                }
         }
     } else {
-        for (int e = tid; e < LP * LP; e += NTHR) {
+        for (int e = tid; e < LP * LP; e += blockDim.x) {
             const double v = (e % LP == e / LP) ? 1.0 : 0.0;
-            a.R64[e] = v;
-            a.R32[e] = (float)v;
+            R64[e] = v;
+            R32[e] = (float)v;
         }
     }
 }
 
-hipError_t launch_chol_inv(int lp, const GroupLaunch<CholArgs>& L, hipStream_t st) {
-    switch (lp) {
-        case 16: hipLaunchKernelGGL(k_chol_blk<1>, dim3(L.count), dim3(64), 0, st, mkg(L)); break;
-        case 32: hipLaunchKernelGGL(k_chol_blk<2>, dim3(L.count), dim3(128), 0, st, mkg(L)); break;
-        case 48: hipLaunchKernelGGL(k_chol_blk<3>, dim3(L.count), dim3(192), 0, st, mkg(L)); break;
-        case 64: hipLaunchKernelGGL(k_chol_blk<4>, dim3(L.count), dim3(256), 0, st, mkg(L)); break;
-        case 80: hipLaunchKernelGGL(k_chol_blk<5>, dim3(L.count), dim3(320), 0, st, mkg(L)); break;
-        case 96: hipLaunchKernelGGL(k_chol_blk<6>, dim3(L.count), dim3(384), 0, st, mkg(L)); break;
-        case 112: hipLaunchKernelGGL(k_chol_blk<7>, dim3(L.count), dim3(448), 0, st, mkg(L)); break;
-        case 128: hipLaunchKernelGGL(k_chol_blk<8>, dim3(L.count), dim3(512), 0, st, mkg(L)); break;
+// Reduction of the partial Gram matrices; with chol.R64 set, the workgroup that ends last goes on to the
+// Cholesky factor and its inverse (a launch and its gap less than a kernel of its own).
+// TPB / 8 entries per workgroup, eight threads per entry: thread t sums the partials w = t, t + 8, ..
+// (independent loads in flight), and the eight sums are combined in a fixed order.
+constexpr int reduce_threads(int nt) { return nt <= 4 ? 256 : 512; }  // a wave per block column at least
+
+template <int NT>
+__global__ __launch_bounds__(reduce_threads(NT)) void k_gram_reduce(Group<GramArgs> g) {
+    if (group_skipped(g)) return;
+    constexpr int TPB = reduce_threads(NT), EPB = TPB / 8, NP = npairs_of(NT), LP = 16 * NT;
+    static_assert(NP * 256 % EPB == 0, "whole tiles");
+    __shared__ double part[8][EPB];
+    const int it = group_item(g.tstart, g.count, blockIdx.x);
+    const GramArgs& ga = g.args[it];
+    if (ga.cond != nullptr && !(*ga.cond & ga.cond_mask)) return;
+    const int el = threadIdx.x % EPB, t = threadIdx.x / EPB;
+    const int e = (blockIdx.x - g.tstart[it]) * EPB + el;
+    const GLOBAL double* src = gbl(ga.Gpart) + e;  // entry e = pair e / 256, element e mod 256
+    constexpr int64_t wstride = (int64_t)NP * 256;
+    const int nwg = ga.nwg;
+    double a4[4] = {0, 0, 0, 0};
+    int w = t;
+    for (; w + 24 < nwg; w += 32)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a4[u] += src[(int64_t)(w + 8 * u) * wstride];
+    for (; w < nwg; w += 8) a4[0] += src[(int64_t)w * wstride];
+    part[t][el] = (a4[0] + a4[1]) + (a4[2] + a4[3]);
+    __syncthreads();
+    if (t == 0) {
+        const double s = ((part[0][el] + part[1][el]) + (part[2][el] + part[3][el])) +
+                         ((part[4][el] + part[5][el]) + (part[6][el] + part[7][el]));
+        const int p = e / 256, mm = (e % 256) / 16, nn = e % 16;
+        int a = 0, q = p;
+        while (q >= NT - a) { q -= NT - a; ++a; }
+        const int b = a + q;
+        // agent scope: written through this XCD's L2 (a fence that writes the whole L2 back from every
+        // workgroup cost 25 us of 30 at lp = 128)
+        GLOBAL double* G = gbl(ga.G);
+        __hip_atomic_store(G + (16 * a + mm) * LP + 16 * b + nn, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(G + (16 * b + nn) * LP + 16 * a + mm, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the entries are out ...
+    }
+    if (ga.chol.R64 == nullptr) return;  // uniform
+    __shared__ __attribute__((aligned(16))) double Rs[NP * CHOL_BLK];
+    __shared__ __attribute__((aligned(16))) double Xs[NT * CHOL_BLK];
+    __shared__ double gd[LP];
+    __shared__ int s_fail, s_last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int* arrived = ga.chol.flags + FLAG_ARRIVED;
+        const int tiles = g.tstart[it + 1] - g.tstart[it];
+        // ... before the workgroup is counted
+        s_last = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tiles - 1;
+        if (s_last) *arrived = 0;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the other workgroups' entries, not older copies
+    chol_body<NT>(ga, CholShared{Rs, Xs, gd, &s_fail});
+}
+
+// Partial workgroups per pair group: one per 4 row blocks, at most `cap`;
+// by default (cap 0) 256 for a single pair group (measured: more partials
+// cost more in the reduction than they save) and about 512 workgroups over
+// several pair groups (two waves per SIMD), rounded down to a multiple of 8.
+int gram_nwg(int64_t M, int cap, int nt) {
+    const int64_t nrb = (M + 15) / 16;
+    int64_t nwg = (nrb + 3) / 4;
+    if (cap < 1 || cap > GRAM_WGS) cap = gram_groups(nt) == 1 ? 256 : (GRAM_WGS / gram_groups(nt)) & ~7;
+    if (nwg > cap) nwg = cap;
+    if (nwg < 1) nwg = 1;
+    return (int)nwg;
+}
+
+int gram_tiles(int nt, int nwg) { return nwg * gram_groups(nt); }
+int gram_reduce_tiles(int nt) { return npairs_of(nt) * 256 / (reduce_threads(nt) / 8); }
+
+template <typename Tin, int NT>
+static hipError_t gram_nt(const GroupLaunch<GramArgs>& L, const GroupLaunch<GramArgs>& R, hipStream_t st) {
+    hipLaunchKernelGGL((k_gram<Tin, NT>), dim3(L.tiles), dim3(256), 0, st, mkg(L));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_gram_reduce<NT>, dim3(R.tiles), dim3(reduce_threads(NT)), 0, st, mkg(R));
+    return hipGetLastError();
+}
+
+template <typename Tin>
+static hipError_t gram_dispatch(int nt, const GroupLaunch<GramArgs>& L, const GroupLaunch<GramArgs>& R,
+                                hipStream_t st) {
+    switch (nt) {
+#define RPOD_GRAM_CASE(K) case K: return gram_nt<Tin, K>(L, R, st);
+        RPOD_GRAM_CASE(1) RPOD_GRAM_CASE(2) RPOD_GRAM_CASE(3) RPOD_GRAM_CASE(4)
+        RPOD_GRAM_CASE(5) RPOD_GRAM_CASE(6) RPOD_GRAM_CASE(7) RPOD_GRAM_CASE(8)
+#undef RPOD_GRAM_CASE
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+}
+
+hipError_t launch_gram(int tin, int nt, const GroupLaunch<GramArgs>& L, const GroupLaunch<GramArgs>& R,
+                       hipStream_t st) {
+    if (tin == DT_F64) return gram_dispatch<double>(nt, L, R, st);
+    if (tin == DT_F32) return gram_dispatch<float>(nt, L, R, st);
+    return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------
