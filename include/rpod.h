@@ -263,10 +263,10 @@ rpod_status rpod_energy(rpod_plan plan, int32_t item, double delta, double* ener
  *          norms over the m cells: the L2 norm on a uniform grid up to the
  *          cell area, which cancels) and the call synchronises the stream;
  *          otherwise it only enqueues.
- * FP32 fields with m a multiple of 4 and out 16-byte aligned are formed on
- * the matrix cores with operands split exactly into BF16 parts (FP32-accurate
- * products, FP32 sums); other fields by fused multiply-adds in dtype. The
- * error's sums run in FP64, fixed order. workspace (device, 256-byte aligned) of at
+ * Fields are formed on the matrix cores: FP64 by fused multiply-adds in the
+ * order of the modes; FP32 with operands split exactly into BF16 parts
+ * (FP32-accurate products, FP32 sums; a field that meets an infinity or a
+ * NaN is not finite). The error's sums run in FP64, fixed order. workspace (device, 256-byte aligned) of at
  * least rpod_reconstruct_workspace_size(m, r) bytes, used only during the call. */
 rpod_status rpod_reconstruct_workspace_size(int64_t m, int32_t r, size_t* bytes);
 rpod_status rpod_reconstruct(int32_t dtype, int64_t m, int32_t r, int64_t T, const void* Phi, const void* mean,
@@ -275,10 +275,9 @@ rpod_status rpod_reconstruct(int32_t dtype, int64_t m, int32_t r, int64_t T, con
 
 /* For callers that cannot allocate (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): rpod_reconstruct without
- * a workspace argument. Same arguments, meaning and results, except that the
- * fields are always formed by fused multiply-adds in dtype (never on the
- * matrix cores, whose operand staging needs a workspace), so FP32 fields may
- * differ from rpod_reconstruct's in the last bits; the error is the same
+ * a workspace argument. Same arguments, meaning and results (FP32 without
+ * the splitting of the coefficients once for all workgroups, which takes the
+ * workspace: a little slower, the same fields); the error is the same
  * computation. Its scratch (the time-averaged coefficients, the partial sums
  * of the error) is a static device array of about 1 MB per GPU, kept until
  * the process ends; the call allocates nothing. m <= 2^24 (RPOD_EINVAL

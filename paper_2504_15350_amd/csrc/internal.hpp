@@ -96,7 +96,7 @@ hipError_t launch_center_y(int tacc, const GroupLaunch<CenterYArgs>& L, hipStrea
 hipError_t launch_center_cross(int tacc, const GroupLaunch<CrossArgs>& L, hipStream_t st);
 hipError_t launch_center_sum(const GroupLaunch<CrossSumArgs>& L, hipStream_t st);  // one tile per entry
 
-// Reconstruction mean + Phi alpha (out may be NULL) and, with ref, the sums
+// Reconstruction mean + Phi alpha (out may be NULL) on the matrix cores and, with ref, the sums
 // ||avg ref - avg recon||^2 and ||avg ref||^2 into out2[0], out2[1] (abar: r
 // doubles, part: 2 ceil(m / 256) doubles of scratch). dt: DT_F64 or DT_F32.
 // Static scratch of rpod_reconstruct_noalloc: layout and the device address of
@@ -107,12 +107,12 @@ hipError_t recon_scratch(double** ptr);
 hipError_t launch_reconstruct(int dt, int64_t m, int r, int64_t T, const void* Phi, const void* mean,
                               const void* alpha, void* out, const void* ref, int64_t ld_ref, double* abar,
                               double* part, double* out2, hipStream_t st);
-// FP32 fields on the matrix cores (m a multiple of 4, out 16-byte aligned):
-// aug (lda x (r + 1), lda = roundup(m, 4)), x (ldx x 128, ldx = roundup(r + 1,
-// 32)), one SxArgs record and two ints of tile table, all device scratch.
+// FP32 fields alone, with op_bytes of device scratch at op for the coefficients split once (6144 bytes
+// for 32 times and 32 modes, the constant one of the mean included); with less they are split by every
+// workgroup, with the same results. The remaining arguments are not used.
 hipError_t launch_reconstruct_mfma(int64_t m, int r, int64_t T, const float* Phi, const float* mean,
-                                   const float* alpha, float* out, float* aug, int64_t lda, float* x, int ldx,
-                                   SxArgs* rec, int* tstart, hipStream_t st);
+                                   const float* alpha, float* out, float* op, int64_t op_bytes, float*, int, SxArgs*,
+                                   int*, hipStream_t st);
 
 // ||S||_F^2 in FP64 (tin: storage type): nwg tiles of partial sums (columns
 // strided over the tiles), then one tile adding them in order.

@@ -1965,9 +1965,7 @@ rpod_status rpod_energy(rpod_plan plan, int32_t item, double delta, double* ener
 // and for FP32 fields on the matrix cores the augmented modes, one chunk's
 // operand and its launch record
 struct ReconLayout {
-    size_t abar, out2, part, aug, x, rec, tstart, total;
-    int64_t lda;
-    int ldx;
+    size_t abar, out2, part, op, op_bytes, total;
 };
 ReconLayout recon_layout(int64_t m, int r) {
     ReconLayout L{};
@@ -1977,15 +1975,14 @@ ReconLayout recon_layout(int64_t m, int r) {
         off += (bytes + 255) / 256 * 256;
         return o;
     };
-    L.lda = roundup(m, 4);
-    L.ldx = (int)roundup(r + 1, 32);
     L.abar = take((size_t)r * 8);
-    L.out2 = take(16);
+    L.out2 = take(32);  // the two sums, then the count of finished tiles
     L.part = take((size_t)2 * ((m + 255) / 256) * 8);
-    L.aug = take((size_t)L.lda * (r + 1) * 4);
-    L.x = take((size_t)L.ldx * 128 * 4);
-    L.rec = take(sizeof(SxArgs));
-    L.tstart = take(2 * sizeof(int));
+    // split coefficients: 192 bytes for a time and 32 modes, for up to 16384 times and no more than the
+    // modes themselves take
+    const size_t step = (size_t)192 * ((r + 32) / 32);
+    L.op_bytes = step * (size_t)std::min<int64_t>(16384, m * 4 * (r + 1) / (int64_t)step / 32 * 32);
+    L.op = take(L.op_bytes);
     L.total = off;
     return L;
 }
@@ -2016,16 +2013,13 @@ rpod_status rpod_reconstruct(int32_t dtype, int64_t m, int32_t r, int64_t T, con
     double* out2 = reinterpret_cast<double*>(ws + RL.out2);
     double* part = reinterpret_cast<double*>(ws + RL.part);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    // FP32 fields on the matrix cores when the output allows 16-byte stores
-    const bool mfma = dtype == RPOD_F32 && out != nullptr && m % 4 == 0 && (uintptr_t)out % 16 == 0;
-    if (mfma)
+    const bool split = dtype == RPOD_F32 && out != nullptr;
+    if (split)
         HIP_TRY(launch_reconstruct_mfma(m, r, T, static_cast<const float*>(Phi), static_cast<const float*>(mean),
                                         static_cast<const float*>(alpha), static_cast<float*>(out),
-                                        reinterpret_cast<float*>(ws + RL.aug), RL.lda,
-                                        reinterpret_cast<float*>(ws + RL.x), RL.ldx,
-                                        reinterpret_cast<SxArgs*>(ws + RL.rec), reinterpret_cast<int*>(ws + RL.tstart),
-                                        st));
-    HIP_TRY(launch_reconstruct(dtype == RPOD_F64 ? DT_F64 : DT_F32, m, r, T, Phi, mean, alpha, mfma ? nullptr : out,
+                                        reinterpret_cast<float*>(ws + RL.op), (int64_t)RL.op_bytes, nullptr, 0, nullptr,
+                                        nullptr, st));
+    HIP_TRY(launch_reconstruct(dtype == RPOD_F64 ? DT_F64 : DT_F32, m, r, T, Phi, mean, alpha, split ? nullptr : out,
                                ref, ld_ref, abar, part, out2, st));
     if (ref != nullptr && eps != nullptr) {
         double h[2] = {0.0, 0.0};

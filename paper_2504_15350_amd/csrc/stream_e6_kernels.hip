@@ -17,60 +17,11 @@
 // MFMA operand layout (16x16x32 bf16, gfx950): lane l supplies
 // A[l%16][8(l/16) + i] and B[8(l/16) + i][l%16], i = 0..7; the result holds
 // D[4(l/16) + v][l%16].
-#include <hip/hip_bf16.h>
-
 #include "device_common.hpp"
 #include "internal.hpp"
+#include "split_ops.hpp"
 
 namespace rpod {
-
-typedef __bf16 e6_bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short e6_u16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ f32x4 mma_bf16(e6_u16x8 a, e6_u16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(e6_bf16x8, a), __builtin_bit_cast(e6_bf16x8, b),
-                                                   c, 0, 0, 0);
-}
-
-typedef float e6_f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 e6_bf16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned e6_u32x4 __attribute__((ext_vector_type(4)));
-
-// Three-way split of two values; each result word packs the parts of a
-// (low half) and b (high half). Rounding to nearest at every level.
-__device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
-    const e6_f32x2 x{a, b};
-    h = __builtin_bit_cast(unsigned, __builtin_convertvector(x, e6_bf16x2));
-    const e6_f32x2 r = x - e6_f32x2{__builtin_bit_cast(float, h << 16), __builtin_bit_cast(float, h & 0xffff0000u)};
-    m = __builtin_bit_cast(unsigned, __builtin_convertvector(r, e6_bf16x2));
-    const e6_f32x2 t = r - e6_f32x2{__builtin_bit_cast(float, m << 16), __builtin_bit_cast(float, m & 0xffff0000u)};
-    l = __builtin_bit_cast(unsigned, __builtin_convertvector(t, e6_bf16x2));
-}
-
-// eight values (x0 then x1) -> the three BF16 operands
-__device__ __forceinline__ void split8(f32x4 x0, f32x4 x1, e6_u16x8& ah, e6_u16x8& am, e6_u16x8& al) {
-    e6_u32x4 h, m, l;
-    unsigned a, b, c;
-    split_pair(x0[0], x0[1], a, b, c); h[0] = a; m[0] = b; l[0] = c;
-    split_pair(x0[2], x0[3], a, b, c); h[1] = a; m[1] = b; l[1] = c;
-    split_pair(x1[0], x1[1], a, b, c); h[2] = a; m[2] = b; l[2] = c;
-    split_pair(x1[2], x1[3], a, b, c); h[3] = a; m[3] = b; l[3] = c;
-    ah = __builtin_bit_cast(e6_u16x8, h);
-    am = __builtin_bit_cast(e6_u16x8, m);
-    al = __builtin_bit_cast(e6_u16x8, l);
-}
-
-// acc += the six leading terms of (ah + am + al)(bh + bm + bl), small terms first
-__device__ __forceinline__ void mma6(const e6_u16x8& ah, const e6_u16x8& am, const e6_u16x8& al, const e6_u16x8& bh,
-                                     const e6_u16x8& bm, const e6_u16x8& bl, f32x4& acc) {
-    f32x4 s = acc;
-    s = mma_bf16(al, bh, s);
-    s = mma_bf16(am, bm, s);
-    s = mma_bf16(ah, bl, s);
-    s = mma_bf16(am, bh, s);
-    s = mma_bf16(ah, bm, s);
-    acc = mma_bf16(ah, bh, s);
-}
 
 // A 16-byte load at any 4-byte alignment: gfx950 global loads need no more, so odd leading
 // dimensions of S take the same path as padded ones (100003 x 2000, ld 100003, 60 columns of X: S X
@@ -89,8 +40,8 @@ typedef float e6_f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 // ---------------------------------------------------------------------------
 constexpr int E6_XLD = 40;  // halfwords per staged X column (32 rows + pad)
 
-// TALL (products with few columns of S, K = 16 nt or r + 1: the tall R^-1 applications, the lift,
-// the reconstruction): the next step's S columns are loaded as soon as the current ones are split,
+// TALL (products with few columns of S, K = 16 nt: the tall R^-1 applications, the lift):
+// the next step's S columns are loaded as soon as the current ones are split,
 // before the matrix-core work (with four steps per workgroup every exposed load latency counts:
 // 1048576 x 128 times 128 x 128, 367 against 393 us); long passes over S keep the loads after the
 // matrix-core work (262144 x 5000 with 64 columns: 1.07 against 1.12 ms).
