@@ -48,13 +48,13 @@ template <> __device__ __forceinline__ int mfma_row<double>(int kg, int v) { ret
 // the matrix; run_fix, shifted into place and zero outside. No branch differs between lanes. (Behind a
 // branch per element the loads wait for each other: 3-7 us per edge step.) Streamed once: non-temporal.
 template <typename E, int N> using run_vec_u = E __attribute__((ext_vector_type(N), aligned(sizeof(E))));
-template <typename E, int N>
+template <typename E, int N, bool LONG = false>  // LONG: lim >= N is known (loads behind a branch each wait)
 __device__ __forceinline__ E __attribute__((ext_vector_type(N)))
 run_load(const GLOBAL E* S, int64_t ld, int64_t lim, int64_t n, int64_t i, int64_t j) {
     typedef E V __attribute__((ext_vector_type(N)));
     typedef run_vec_u<E, N> VU;
     const GLOBAL E* col = S + (j < n ? j : n - 1) * ld;
-    if (lim >= N)  // uniform
+    if (LONG || lim >= N)  // uniform
         return (V)__builtin_nontemporal_load(reinterpret_cast<const GLOBAL VU*>(col + (i < lim - N ? i : lim - N)));
     V v;
 #pragma unroll

@@ -145,10 +145,16 @@ __device__ __forceinline__ void sx16_body(const GLOBAL unsigned short* __restric
         for (int64_t j0 = 0; j0 < n; j0 += SX16_BK) {
             __syncthreads();  // previous chunk fully consumed
             if (edge(j0)) {
+                const int64_t i = i0 + 8 * rg, j = j0 + cc;
+                if (m >= 8) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) st[q] = run_load<unsigned short, 8>(S, ldS, m, n, i0 + 8 * rg, j0 + cc + 8 * q);
+                    for (int q = 0; q < 4; ++q) st[q] = run_load<unsigned short, 8, true>(S, ldS, m, n, i, j + 8 * q);
+                } else {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) st[q] = run_fix<unsigned short, 8>(st[q], m, n, i0 + 8 * rg, j0 + cc + 8 * q);
+                    for (int q = 0; q < 4; ++q) st[q] = run_load<unsigned short, 8>(S, ldS, m, n, i, j + 8 * q);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) st[q] = run_fix<unsigned short, 8>(st[q], m, n, i, j + 8 * q);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {

@@ -29,23 +29,37 @@ namespace rpod {
 typedef float e6_f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // ---------------------------------------------------------------------------
-// Y = S X. Workgroup = 4 waves = 256 rows. Per 32-column step lane (r, g)
-// of a wave holds rows 4 r .. 4 r + 3 of columns j0 + 8 g + i, i = 0..7 (a
-// wave instruction covers 4 columns x 256 bytes); element t of these is the
-// A operand of row tile t (MFMA row r of tile t is row 4 r + t of the wave),
-// K index 8 g + i. The step's block of X (32 rows x 16 NT columns, read in
-// FP32 and split into its three BF16 parts as it is staged) is kept in LDS,
-// double-buffered, and shared by the four waves. All four tiles are split before the matrix-core work, and the next
-// step's S columns are loaded after it.
+// Y = S X. Workgroup = W waves = 256 rows, U = 16 / W row tiles per wave. Per
+// 32-column step lane (r, g) of a wave holds rows U r .. U r + U - 1 of columns
+// j0 + 8 g + i, i = 0..7 (a wave instruction covers 4 columns x 64 U bytes);
+// element t of these is the A operand of row tile t (MFMA row r of tile t is row
+// U r + t of the wave), K index 8 g + i. The step's block of X (32 rows x 16 NT
+// columns, read in FP32 and split into its three BF16 parts as it is staged) is
+// kept in LDS, double-buffered, and shared by the waves. All tiles are split before
+// the matrix-core work.
+// Bound by the reads of S up to 64 columns of X, by the matrix cores beyond (and
+// there by the loads and splits that a SIMD's one or two waves leave exposed).
+// Waves: four of four tiles, whose operand reads from LDS serve four products
+// each; at 128 columns these take more than half of the register file and leave
+// one wave per SIMD, and eight of two tiles are the faster (262144 x 1000: 376
+// against 484 us, 65536 x 3000: 272 against 358; 1048576 x 128 times 128 x 128:
+// 338 against 387; at 112 columns, where two waves still fit, 581 against 459 at
+// 131072 x 3500). Every entry has the same order of sums in either.
 // ---------------------------------------------------------------------------
 constexpr int E6_XLD = 40;  // halfwords per staged X column (32 rows + pad)
+// (EN sums S's squares in an order that belongs to four waves)
+constexpr int sx_waves(int nt, bool en) { return nt == 8 && !en ? 8 : 4; }
+// EARLY: the next step's S columns are loaded as soon as the current ones are split, before the
+// matrix-core work; else after it. Early in products with few columns of S (the tall R^-1 applications,
+// the lift: with four steps per workgroup every exposed load latency counts), with one workgroup per CU
+// or less, which has no other to hide the loads (20000 x 1000, 60 columns: 65 against 75 us; 5003 x 701:
+// 45 against 51), at 16 columns (131072 x 2000: 164 against 173) and at 128 (65536 x 3000 with four waves:
+// 304 against 349 us); else late (262144 x 5000, 60 columns: 1043 against 1052 us; 100003 x 2000: 194
+// against 200; 131072 x 3500, 110 columns: 459 against 486).
+constexpr int64_t SX_FEW_TILES = 256;
+constexpr bool sx_early_always(int nt) { return nt == 1 || nt == 8; }
 
-// TALL (products with few columns of S, K = 16 nt: the tall R^-1 applications, the lift):
-// the next step's S columns are loaded as soon as the current ones are split,
-// before the matrix-core work (with four steps per workgroup every exposed load latency counts:
-// 1048576 x 128 times 128 x 128, 367 against 393 us); long passes over S keep the loads after the
-// matrix-core work (262144 x 5000 with 64 columns: 1.07 against 1.12 ms).
-template <int NT, bool EN = false, bool TALL = false>
+template <int NT, bool EN, bool EARLY, int W>
 __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, int64_t m, int64_t n,
                                            const GLOBAL float* __restrict__ X, int64_t ldX,
                                            GLOBAL float* Y, int64_t ldY, int64_t mstore, int cmax, int64_t bx,
@@ -53,40 +67,45 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
     constexpr int XPART = 16 * NT * E6_XLD;     // one staged part
     constexpr int XB = 3 * XPART;               // one staged X block (three parts)
     constexpr int XCH = 16 * NT * 8;            // 16-byte FP32 chunks of a block (4 rows each)
-    constexpr int XPT = (XCH + 255) / 256;
+    constexpr int U = 16 / W;                   // row tiles per wave
+    constexpr int NTHR = 64 * W, XPT = (XCH + NTHR - 1) / NTHR;
+    typedef float Vec __attribute__((ext_vector_type(U)));
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, g = lane >> 4;
-    const int64_t iw = bx * 256 + wave * 64;
-    const int64_t irow = iw + 4 * r16;
+    const int64_t iw = bx * (16 * U * W) + wave * (16 * U);
+    const int64_t irow = iw + U * r16;
     // Unguarded vector loads, a uniform base per column plus a 32-bit lane offset. A wave with rows past
     // m takes whole runs too (rows of the column's padding or of the next column, which meet only
     // output rows past m, written as zero), except where the last column of S is in the step, whose
     // runs could leave S, or a column is shorter than a tile.
-    const bool inside = iw + 64 <= m, fast = (inside || ldS >= 256) && ldS < ((int64_t)1 << 25);
+    const bool inside = iw + 16 * U <= m, fast = (inside || ldS >= 256) && ldS < ((int64_t)1 << 25);
     auto plain = [&](int64_t j0) { return fast && j0 + 32 <= (inside ? n : n - 1); };
     const uint32_t so = (uint32_t)(8 * g) * (uint32_t)(4 * ldS) + (uint32_t)(4 * irow);
-    f32x4 acc[4][NT];
+    f32x4 acc[U][NT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < U; ++t)
 #pragma unroll
         for (int c = 0; c < NT; ++c) acc[t][c] = f32x4{0, 0, 0, 0};
-    f32x4 sv[8];
+    Vec sv[8];
     auto load_s = [&](int64_t j0) {
         if (plain(j0)) {
             const GLOBAL char* p = reinterpret_cast<const GLOBAL char*>(S + j0 * ldS);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                sv[i] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL e6_f32x4u*>(p + 4 * i * ldS + so));
+                sv[i] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL run_vec_u<float, U>*>(p + 4 * i * ldS + so));
+        } else if (m >= U) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sv[i] = run_load<float, U, true>(S, ldS, m, n, irow, j0 + 8 * g + i);
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sv[i] = run_load<float, 4>(S, ldS, m, n, irow, j0 + 8 * g + i);
+            for (int i = 0; i < 8; ++i) sv[i] = run_load<float, U>(S, ldS, m, n, irow, j0 + 8 * g + i);
         }
     };
     f32x4 xr[XPT];
     auto load_x = [&](int64_t j0) {
 #pragma unroll
         for (int q = 0; q < XPT; ++q) {
-            const int ch = tid + 256 * q;
+            const int ch = tid + NTHR * q;
             if (ch < XCH) xr[q] = *reinterpret_cast<const GLOBAL f32x4*>(X + (int64_t)(ch >> 3) * ldX + j0 + 4 * (ch & 7));
         }
     };
@@ -95,7 +114,7 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
     auto put_x = [&](int buf) {
 #pragma unroll
         for (int q = 0; q < XPT; ++q) {
-            const int ch = tid + 256 * q;
+            const int ch = tid + NTHR * q;
             if (ch < XCH) {
                 unsigned h0, m0, l0, h1, m1, l1;
                 split_pair(xr[q][0], xr[q][1], h0, m0, l0);
@@ -116,27 +135,27 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
         const bool more = j0 + 32 < n;
         if (!plain(j0)) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sv[i] = run_fix<float, 4>(sv[i], m, n, irow, j0 + 8 * g + i);
+            for (int i = 0; i < 8; ++i) sv[i] = run_fix<float, U>(sv[i], m, n, irow, j0 + 8 * g + i);
         }
         if constexpr (EN) {
             float p = 0.0f;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < U; ++t) {
                     const float x = inside || irow + t < m ? sv[i][t] : 0.0f;
                     p = fmaf(x, x, p);
                 }
             sq += (double)p;
         }
-        e6_u16x8 ah[4], am[4], al[4];
+        e6_u16x8 ah[U], am[U], al[U];
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < U; ++t)
             split8(f32x4{sv[0][t], sv[1][t], sv[2][t], sv[3][t]}, f32x4{sv[4][t], sv[5][t], sv[6][t], sv[7][t]}, ah[t],
                    am[t], al[t]);
         if (more) {
             load_x(j0 + 32);
-            if (TALL) load_s(j0 + 32);  // sv is free once split
+            if (EARLY) load_s(j0 + 32);  // sv is free once split
         }
         __syncthreads();  // block buf staged
 #pragma unroll
@@ -146,10 +165,10 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
             const e6_u16x8 bm = *reinterpret_cast<const e6_u16x8*>(xb + XPART);
             const e6_u16x8 bl = *reinterpret_cast<const e6_u16x8*>(xb + 2 * XPART);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) mma6(ah[t], am[t], al[t], bh, bm, bl, acc[t][c]);
+            for (int t = 0; t < U; ++t) mma6(ah[t], am[t], al[t], bh, bm, bl, acc[t][c]);
         }
         if (more) {
-            if (!TALL) load_s(j0 + 32);
+            if (!EARLY) load_s(j0 + 32);
             put_x(buf ^ 1);  // block buf ^ 1 was last read before this step's barrier
             buf ^= 1;
         }
@@ -162,17 +181,19 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
         GLOBAL float* py = Y + (int64_t)(16 * c + r16) * ldY;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int64_t row = iw + 4 * (4 * g + v);
-            f32x4 o{acc[0][c][v], acc[1][c][v], acc[2][c][v], acc[3][c][v]};
+            const int64_t row = iw + U * (4 * g + v);
+            Vec o;
+#pragma unroll
+            for (int t = 0; t < U; ++t) o[t] = acc[t][c][v];
             if (!inside) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) o[t] = row + t < m ? o[t] : 0.0f;
+                for (int t = 0; t < U; ++t) o[t] = row + t < m ? o[t] : 0.0f;
             }
-            if (row + 3 < mstore) {
-                *reinterpret_cast<GLOBAL f32x4*>(py + row) = o;
+            if (row + U <= mstore) {
+                *reinterpret_cast<GLOBAL Vec*>(py + row) = o;
             } else {
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
+                for (int t = 0; t < U; ++t)
                     if (row + t < mstore) py[row + t] = o[t];
             }
         }
@@ -181,10 +202,12 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
 
 // EN: the energy report's variant (also each tile's sum of squares of S, in
 // a fixed order: per lane, then a tree over the workgroup)
-template <int NT, bool EN = false, bool TALL = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2 : 1, 2))) void k_sx_e6(
+template <int NT, bool EN, bool EARLY>
+__global__ __launch_bounds__(64 * sx_waves(NT, EN))
+__attribute__((amdgpu_waves_per_eu(EN && NT == 8 ? 1 : 2, sx_waves(NT, EN) == 8 ? 4 : 2))) void k_sx_e6(
     Group<SxArgs> g) {
     if (group_skipped(g)) return;
+    constexpr int W = sx_waves(NT, EN);
     __shared__ __attribute__((aligned(16))) unsigned short xs[2 * 3 * 16 * NT * E6_XLD];
     const int it = group_item(g.tstart, g.count, blockIdx.x);
     const SxArgs& a = g.args[it];
@@ -193,7 +216,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2
     if constexpr (EN) {
         __shared__ double red[256];
         double sq = 0.0;
-        sx_e6_body<NT, true>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.X), a.ldX,
+        sx_e6_body<NT, true, EARLY, W>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.X), a.ldX,
                                   gbl((float*)a.Y), a.ldY, a.mstore, a.cmax > 0 ? a.cmax : 16 * NT,
                                   blockIdx.x - g.tstart[it], xs, &sq);
         red[threadIdx.x] = sq;
@@ -204,15 +227,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2
         }
         if (threadIdx.x == 0 && a.fpart != nullptr) a.fpart[blockIdx.x - g.tstart[it]] = red[0];
     } else {
-        sx_e6_body<NT, false, TALL>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.X), a.ldX,
+        sx_e6_body<NT, false, EARLY, W>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.X), a.ldX,
                                          gbl((float*)a.Y), a.ldY, a.mstore, a.cmax > 0 ? a.cmax : 16 * NT,
                                          blockIdx.x - g.tstart[it], xs);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Z_s = S^T Q. Workgroup: 256 columns of S (four column tiles of 16 per
-// wave), 32 rows per step; the step's S block (32 x 256, FP32) and the three
+// Z_s = S^T Q. Workgroup: 256 columns of S (16 / W column tiles of 16
+// for each of the W waves), 32 rows per step; the step's S block (32 x 256, FP32) and the three
 // BF16 parts of the Q block (32 x 16 NT, read as FP32 and split when staged)
 // are staged in LDS column-major and the next step's blocks are loaded into
 // registers during the matrix-core work. Lane (r, g) reads rows 8 g .. 8 g + 7
@@ -232,17 +255,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 2
 // ---------------------------------------------------------------------------
 constexpr int E6_R = 32, E6_LDS = E6_R, E6_LDQ = E6_R, E6_HB = 256;
 
-template <int NT>
+// Waves per workgroup: four of four column tiles while two of them fit a SIMD's registers (two workgroups
+// per CU); at 112 and 128 columns of Q they do not, and eight of two tiles hide more of the loads and
+// splits than one such wave (65536 x 3000, 128 columns: 335 -> 300 us; 131072 x 3500, 110 columns: 660 ->
+// 597; but at 80 columns 40000 x 4000 204 against 178 us, at 60 262144 x 5000 1170 against 1108). Two LDS
+// buffers and one barrier per step measured no better (349 against 363 us at 262144 x 1000 with 128
+// columns, 612 against 590 with 110, 1242 against 1108 at 262144 x 5000 with 60).
+constexpr int stq_waves(int nt, bool lines) { return lines && nt >= 7 ? 8 : 4; }
+
+template <int NT, int W>
 __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, int64_t ldS, int64_t m, int64_t n,
                                             const GLOBAL float* __restrict__ Q, int64_t ldQ,
                                             GLOBAL float* __restrict__ Zp, int64_t nP, int nsplit, int ncb,
                                             int tile, float* ss, unsigned short* qs) {
-    constexpr int R = E6_R, LD = E6_LDS, LDQ = E6_LDQ, HB = E6_HB, U = HB / 64;
+    constexpr int R = E6_R, LD = E6_LDS, LDQ = E6_LDQ, HB = E6_HB, U = HB / (16 * W), NTHR = 64 * W;
     constexpr int CPC = R / 4;                  // 16-byte S chunks per column
-    constexpr int SPT = HB * CPC / 256;         // S chunks per thread
+    constexpr int SPT = HB * CPC / NTHR;       // S chunks per thread
     constexpr int QCPC = R / 4;                 // 16-byte FP32 Q chunks per column
     constexpr int QCH = 16 * NT * QCPC;         // Q chunks per step
-    constexpr int QPT = (QCH + 255) / 256;
+    constexpr int QPT = (QCH + NTHR - 1) / NTHR;
     constexpr int QPART = 16 * NT * LDQ;        // halfwords per staged part
     const int cb = tile % ncb, sp = tile / ncb;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -260,8 +291,8 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
 
     f32x4 sr[SPT];
     f32x4 qr[QPT];
-    // chunk q of a thread: column j0 + tid / CPC + q (256 / CPC), rows 4 (tid mod CPC) .. +3 of the step
-    constexpr int CSTEP = 256 / CPC;
+    // chunk q of a thread: column j0 + tid / CPC + q (NTHR / CPC), rows 4 (tid mod CPC) .. +3 of the step
+    constexpr int CSTEP = NTHR / CPC;
     const GLOBAL float* sbase = S + (j0 + tid / CPC) * ldS + 4 * (tid % CPC);
     auto fetch = [&](int64_t i0) {
         if (j0 + HB <= n) {  // whole step in range: one unguarded vector load per chunk
@@ -281,8 +312,8 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
     auto fetch_q = [&](int64_t i0) {
 #pragma unroll
         for (int q = 0; q < QPT; ++q) {
-            const int ch = tid + 256 * q;
-            if (QCH % 256 == 0 || ch < QCH)
+            const int ch = tid + NTHR * q;
+            if (QCH % NTHR == 0 || ch < QCH)
                 qr[q] = *reinterpret_cast<const GLOBAL f32x4*>(Q + (int64_t)(ch / QCPC) * ldQ + i0 + 4 * (ch % QCPC));
         }
     };
@@ -290,18 +321,23 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
     auto put_s = [&]() {
 #pragma unroll
         for (int q = 0; q < SPT; ++q) {
-            const int ch = tid + 256 * q, col = ch / CPC;
+            const int ch = tid + NTHR * q, col = ch / CPC;
             *reinterpret_cast<f32x4*>(ss + col * LD + 4 * ((ch % CPC) ^ ((col >> 1) & 7))) = sr[q];
         }
     };
     // a last step past row m (rows past m must count as zero against any padding of S)
     auto put_edge = [&](int64_t i0) {
+        const int64_t i = i0 + 4 * (tid % CPC), j = j0 + tid / CPC;
+        if (m >= 4) {
+#pragma unroll
+            for (int q = 0; q < SPT; ++q) sr[q] = run_load<float, 4, true>(S, ldS, m, n, i, j + CSTEP * q);
+        } else {
+#pragma unroll
+            for (int q = 0; q < SPT; ++q) sr[q] = run_load<float, 4>(S, ldS, m, n, i, j + CSTEP * q);
+        }
 #pragma unroll
         for (int q = 0; q < SPT; ++q)
-            sr[q] = run_load<float, 4>(S, ldS, m, n, i0 + 4 * (tid % CPC), j0 + tid / CPC + CSTEP * q);
-#pragma unroll
-        for (int q = 0; q < SPT; ++q)
-            sr[q] = run_fix<float, 4>(sr[q], m, n, i0 + 4 * (tid % CPC), j0 + tid / CPC + CSTEP * q);
+            sr[q] = run_fix<float, 4>(sr[q], m, n, i, j + CSTEP * q);
         put_s();
     };
     auto put_q = [&]() {
@@ -310,8 +346,8 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
         typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
         for (int q = 0; q < QPT; ++q) {
-            const int ch = tid + 256 * q, col = ch / QCPC, k = ch % QCPC;
-            if (QCH % 256 == 0 || ch < QCH) {
+            const int ch = tid + NTHR * q, col = ch / QCPC, k = ch % QCPC;
+            if (QCH % NTHR == 0 || ch < QCH) {
                 unsigned h0, m0, l0, h1, m1, l1;
                 split_pair(qr[q][0], qr[q][1], h0, m0, l0);
                 split_pair(qr[q][2], qr[q][3], h1, m1, l1);
@@ -560,7 +596,8 @@ __device__ __forceinline__ void stq_e6u_body(const GLOBAL float* __restrict__ S,
 
 // LINES: S's columns start on 128-byte lines
 template <int NT, bool LINES>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= (LINES ? 4 : 6) ? 2 : 1, 2))) void k_stq_e6(
+__global__ __launch_bounds__(64 * stq_waves(NT, LINES)) __attribute__((amdgpu_waves_per_eu(
+    NT <= 6 || stq_waves(NT, LINES) == 8 ? 2 : 1, 2))) void k_stq_e6(
     Group<StqArgs> g) {
     if (group_skipped(g)) return;
     __shared__ __attribute__((aligned(16))) float ss[E6_HB * E6_LDS];  // = 128 x 64
@@ -573,7 +610,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= (LINE
     const int local = blockIdx.x - g.tstart[it], ntl = a.ncb * a.nsplit;
     const int tile = ((ntl & 7) == 0 && (g.tstart[it] & 7) == 0) ? (local & 7) * (ntl >> 3) + (local >> 3) : local;
     if constexpr (LINES)
-        stq_e6_body<NT>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.Q), a.ldQ, gbl((float*)a.Zp),
+        stq_e6_body<NT, stq_waves(NT, true)>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.Q), a.ldQ, gbl((float*)a.Zp),
                         a.nP, a.nsplit, a.ncb, tile, ss, qs);
     else
         stq_e6u_body<NT>(gbl((const float*)S), a.ldS, a.m, a.n, gbl((const float*)a.Q), a.ldQ, gbl((float*)a.Zp),
@@ -597,12 +634,13 @@ static Group<A> mke6(const GroupLaunch<A>& L) {
 
 template <int NT>
 static hipError_t sxe6_nt(const GroupLaunch<SxArgs>& L, bool en, bool tall, hipStream_t st) {
-    if (tall)
-        hipLaunchKernelGGL((k_sx_e6<NT, false, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
-    else if (en)
-        hipLaunchKernelGGL((k_sx_e6<NT, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
+    constexpr int NTHR = 64 * sx_waves(NT, false);
+    if (en)
+        hipLaunchKernelGGL((k_sx_e6<NT, true, false>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
+    else if (tall || sx_early_always(NT) || L.tiles <= SX_FEW_TILES)
+        hipLaunchKernelGGL((k_sx_e6<NT, false, true>), dim3(L.tiles), dim3(NTHR), 0, st, mke6(L));
     else
-        hipLaunchKernelGGL((k_sx_e6<NT>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
+        hipLaunchKernelGGL((k_sx_e6<NT, false, sx_early_always(NT)>), dim3(L.tiles), dim3(NTHR), 0, st, mke6(L));
     return hipGetLastError();
 }
 
@@ -619,7 +657,7 @@ hipError_t launch_sx_e6(int nt, bool /*vec*/, bool en, bool tall, const GroupLau
 template <int NT>
 static hipError_t stqe6_nt(const GroupLaunch<StqArgs>& L, bool lines, hipStream_t st) {
     if (lines)
-        hipLaunchKernelGGL((k_stq_e6<NT, true>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
+        hipLaunchKernelGGL((k_stq_e6<NT, true>), dim3(L.tiles), dim3(64 * stq_waves(NT, true)), 0, st, mke6(L));
     else
         hipLaunchKernelGGL((k_stq_e6<NT, false>), dim3(L.tiles), dim3(256), 0, st, mke6(L));
     return hipGetLastError();

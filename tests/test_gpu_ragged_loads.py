@@ -47,3 +47,18 @@ def test_ragged(m, n, r, p, ld, dtype):
     ref = orpod.rpod_stable(Sr.double().numpy().T, r, sketch_for(11, n, r + p, dtype), 1)
     assert all(np.isfinite(x).all() for x in gpu)
     compare(gpu, ref[:3], dtype, r, ref[3]["ritz"])
+
+
+@pytest.mark.parametrize("m,ld", [(65280, 65280), (65537, 65568), (66001, 66001)])  # 255, 257 and 258 row tiles
+@pytest.mark.parametrize("l", [16, 64, 90, 112, 128])
+def test_fp32_wave_shapes(m, ld, l):
+    """FP32: the products' waves per workgroup and the point of their loads go by the columns and the row tiles."""
+    n = 150
+    g = synth.lowrank_exp(m, n, decay=0.05, noise_std=1e-5, seed=m + l)
+    Sr = round_to(g["St"], torch.float32)
+    buf = torch.full((n, ld), float("nan"), dtype=torch.float32)
+    buf[:, :m] = Sr
+    print(f"[case] m={m} l={l} ld={ld}", flush=True)
+    gpu = run_gpu(buf.to(DEV), m, n, l - 8, 8, 1, 11, torch.float32)
+    ref = orpod.rpod_stable(Sr.double().numpy().T, l - 8, sketch_for(11, n, l, torch.float32), 1)
+    compare(gpu, ref[:3], torch.float32, l - 8, ref[3]["ritz"])
