@@ -437,9 +437,11 @@ rpod_status rpod_warm_residuals(rpod_plan plan, double* rho_modes);
  * (sigma_1^2 + .. + sigma_r^2) / ||S||_F^2 >= delta (-1 if none). Omega_i
  * are columns i b .. i b + b - 1 of the sketch of `seed` (the columns
  * rpod_compute would use with l = l_max). With q = 0 the l columns of Q span
- * S Omega[:, :l], as in rpod_compute with that l. The whole loop, the stopping
- * test included, runs on the device in one launch graph: blocks after the
- * stop and the finishes for other widths are skipped launches.
+ * S Omega[:, :l], as in rpod_compute with that l. In a call that only enqueues
+ * the whole loop, the stopping test included, runs on the device in one launch
+ * graph: blocks after the stop and the finishes for other widths are skipped
+ * launches. A call that waits for its result reads the test after each block
+ * and leaves them out; the results are the same.
  * desc: m, n, ld, dtype as for rpod_compute; r = l_max (a multiple of p, at
  * most 128 and at most min(m, n)); p = b (a positive multiple of 16); q
  * >= 0 power iterations per block; flags 0; block_cols 0. 0 < delta <= 1.
