@@ -77,7 +77,8 @@ hipError_t launch_split16(int tin, const GroupLaunch<SplitArgs>& L, hipStream_t 
 //   rows (split s: rows 64 (k nsplit + s) .., k = 0, 1, ..), nP a multiple
 //   of stq_e6_block_cols(); nsplit a multiple of 8 keeps each split's column
 //   blocks on one XCD. Any 4-byte aligned S; vec: its columns start on
-//   128-byte lines (picks the step shape, not the result).
+//   128-byte lines, or S or Q is too tall for 32-bit offsets (picks the step
+//   shape, not the result; without it chunk_offset_fits(ldS) and (ldQ)).
 // en: also write each tile's sum of the squares of the S entries it read to fpart[tile]
 // tall (not with en): products with few columns of S, the next step's loads issued early
 hipError_t launch_sx_e6(int nt, bool vec, bool en, bool tall, const GroupLaunch<SxArgs>& L, hipStream_t st);

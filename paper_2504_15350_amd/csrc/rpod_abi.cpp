@@ -17,6 +17,7 @@
 
 #include "../../include/rpod.h"
 #include "internal.hpp"
+#include "offsets.hpp"
 #include "warm_model.hpp"
 
 using namespace rpod;
@@ -488,13 +489,16 @@ struct Recorder {
         Step s{s16 ? K_STQ16 : f32 ? K_STQE6 : K_STQ};
         s.tin = L0().tin; s.nt = L0().nt; s.lo = s16 && lo; s.pass = s.lo ? 2 : 1;
         s.vec = true;
+        bool wide = false;  // FP32: operands too tall for the 32-bit offsets of the steps for columns off the lines
         for (const Item* it : C) {
             // FP32: columns on 128-byte lines pick the step shape; otherwise 16-byte loads
             s.vec = s.vec && (it->d.ld % (s16 ? 8 : f32 ? 32 : 4) == 0);
+            wide = wide || (f32 && !chunk_offset_fits(std::max(it->d.ld, it->L.mP)));
             const double sz = (double)dt_size(it->L.tin);
             s.bytes += (double)it->d.m * it->d.n * sz + (double)it->d.n * it->L.l * sz + (double)it->d.m * it->L.l * 4.0;
             s.flops += 2.0 * it->d.m * it->d.n * it->L.l;
         }
+        s.vec = s.vec || wide;
         std::vector<StqArgs> args = each([&](const Item& it) {
             StqArgs a{};
             a.S = nullptr; a.ldS = it.d.ld; a.m = it.d.m; a.n = it.d.n;

@@ -19,6 +19,7 @@
 // D[4(l/16) + v][l%16].
 #include "device_common.hpp"
 #include "internal.hpp"
+#include "offsets.hpp"
 #include "split_ops.hpp"
 
 namespace rpod {
@@ -78,9 +79,9 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
     // m takes whole runs too (rows of the column's padding or of the next column, which meet only
     // output rows past m, written as zero), except where the last column of S is in the step, whose
     // runs could leave S, or a column is shorter than a tile.
-    const bool inside = iw + 16 * U <= m, fast = (inside || ldS >= 256) && ldS < ((int64_t)1 << 25);
+    const bool inside = iw + 16 * U <= m, fast = (inside || ldS >= 256) && row_offset_fits(ldS);
     auto plain = [&](int64_t j0) { return fast && j0 + 32 <= (inside ? n : n - 1); };
-    const uint32_t so = (uint32_t)(8 * g) * (uint32_t)(4 * ldS) + (uint32_t)(4 * irow);
+    const uint32_t so = row_offset(g, ldS, irow);
     f32x4 acc[U][NT];
 #pragma unroll
     for (int t = 0; t < U; ++t)
@@ -299,13 +300,13 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
             const GLOBAL float* p = sbase + i0;
 #pragma unroll
             for (int q = 0; q < SPT; ++q)
-                sr[q] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL f32x4*>(p + CSTEP * q * ldS));
+                sr[q] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL e6_f32x4u*>(p + CSTEP * q * ldS));
         } else {  // columns past n read column n - 1 and are written as zero at the end
 #pragma unroll
             for (int q = 0; q < SPT; ++q) {
                 const int jl = min(tid / CPC + CSTEP * q, (int)(n - 1 - j0));
                 sr[q] = __builtin_nontemporal_load(
-                    reinterpret_cast<const GLOBAL f32x4*>(S + (j0 + jl) * ldS + i0 + 4 * (tid % CPC)));
+                    reinterpret_cast<const GLOBAL e6_f32x4u*>(S + (j0 + jl) * ldS + i0 + 4 * (tid % CPC)));
             }
         }
     };
@@ -424,7 +425,9 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
 // order of every entry is the one above. 100003 x 2000, 60 columns, ld 100003 /
 // 100008: 293 / 268 -> 240 / 232 us; with columns on lines the steps above are
 // the faster (131072 x 2000: 240 against 264 us), because here a staged Q
-// operand serves two column tiles instead of four.
+// operand serves two column tiles instead of four. S or Q of 2^26 rows and more
+// stays with the steps above: a thread's columns here lie within a 32-bit offset
+// of a uniform base, which in 64 bits takes registers that 96 columns do not have.
 // The S block (128 x 64, FP32) of a step and once per unit the parts of the Q
 // block (64 x 16 NT) are staged in LDS column-major. Wave w owns columns 32 w ..
 // 32 w + 31 of each half (two column tiles). S column c holds its 16-byte
@@ -463,16 +466,16 @@ __device__ __forceinline__ void stq_e6u_body(const GLOBAL float* __restrict__ S,
     f32x4 sr[SPT];
     f32x4 qr[QPT];
     // chunk q of a thread: column (of the half) tid / CPC + q (256 / CPC), rows 4 (tid mod CPC) .. + 3.
-    // Addresses are a uniform base per chunk plus one 32-bit offset per thread (narrow: it fits).
+    // Addresses are a uniform base per chunk plus one 32-bit offset per thread (the launch goes to the
+    // other steps where it does not fit).
     constexpr int CSTEP = 256 / CPC;
     const int tc = tid / CPC, tk = tid % CPC;
-    const bool narrow = ldS < ((int64_t)1 << 26);
-    const uint32_t so = (uint32_t)tc * (uint32_t)(4 * ldS) + 16 * tk, qo = (uint32_t)tc * (uint32_t)(4 * ldQ) + 16 * tk;
+    const uint32_t so = chunk_offset(tc, ldS, tk), qo = chunk_offset(tc, ldQ, tk);
     const int sws = sw_s(tc), swq = sw_q(tc);  // of every column tc + 16 q
     auto fetch_s = [&](int64_t i0, int h) {
         const int64_t jh = j0 + E6U_HC * h;
         if (i0 + R > m) return;  // a last unit past row m is loaded when it is staged
-        if (narrow && jh + E6U_HC <= n) {  // the whole step in range: unguarded vector loads
+        if (jh + E6U_HC <= n) {  // the whole step in range: unguarded vector loads
             const GLOBAL char* p = reinterpret_cast<const GLOBAL char*>(S + jh * ldS + i0);
 #pragma unroll
             for (int q = 0; q < SPT; ++q)
