@@ -265,8 +265,10 @@ rpod_status rpod_energy(rpod_plan plan, int32_t item, double delta, double* ener
  *          otherwise it only enqueues.
  * Fields are formed on the matrix cores: FP64 by fused multiply-adds in the
  * order of the modes; FP32 with operands split exactly into BF16 parts
- * (FP32-accurate products, FP32 sums; a field that meets an infinity or a
- * NaN is not finite). The error's sums run in FP64, fixed order. workspace (device, 256-byte aligned) of at
+ * (FP32-accurate products, FP32 sums). FP32 fields with an operand that may
+ * have no such split (an infinity, a NaN, a value within 2^-8 of the largest
+ * or other than zero and below 2^-110) are formed by FP32 fused multiply-adds
+ * in the order of the modes. The error's sums run in FP64, fixed order. workspace (device, 256-byte aligned) of at
  * least rpod_reconstruct_workspace_size(m, r) bytes, used only during the call. */
 rpod_status rpod_reconstruct_workspace_size(int64_t m, int32_t r, size_t* bytes);
 rpod_status rpod_reconstruct(int32_t dtype, int64_t m, int32_t r, int64_t T, const void* Phi, const void* mean,
