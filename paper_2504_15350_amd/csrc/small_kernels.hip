@@ -786,11 +786,21 @@ __device__ __forceinline__ void fma16_bcast(double (&a)[16], double x, double m)
         : "v"(x), "v"(m));
 }
 
+// sqrt(x) for x > 0 and 1 / x: the hardware estimates with one step that cubes their error
+__device__ __forceinline__ double sqrt_3(double x) {
+    const double y = __builtin_amdgcn_rsq(x), z = x * y, e = fma(-z, y, 1.0);
+    return fma(z * e, fma(e, 0.375, 0.5), z);
+}
+__device__ __forceinline__ double rcp_3(double x) {
+    const double y = __builtin_amdgcn_rcp(x), e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
 // One rotation per group of eight lanes that makes the columns own and part (RPL rows per lane)
 // orthogonal: own' = c own - s part, part' = s own + c part; no, np are their squared norms. The
-// half-angle tangent u comes from the hardware estimates (2^-23: that fraction of the inner product
-// removed is left over); c = (1 - u^2) / (1 + u^2) and s = 2 u / (1 + u^2) follow from u to FP64, so
-// the rotation is orthogonal to rounding whatever the error of u.
+// half-angle tangent u, the tangent t, s = 2 u / (1 + u^2) and c = 1 - u s are taken to FP64. (u and t by the estimates alone, 2^-23, leave that fraction of the inner product over: the
+// sweeps take 6 to 9 % less, but the modes of a 16 x 16 factor are 19 % further from the exact ones,
+// and c = (1 - u^2) / (1 + u^2) makes sigma's error half as large again.)
 // SYM: the two groups of a pair within a block compute the same rotation, each as "own"; every
 // expression is then symmetric (or antisymmetric) in the exchange bit for bit, `low` deciding where
 // the norms are equal. Otherwise the update is three shears in place, (1 -u; 0 1) (1 0; s 1) (1 -u; 0 1).
@@ -812,22 +822,17 @@ __device__ __forceinline__ bool jacobi_rotate(double (&own)[RPL], double (&part)
     const double e2 = ga + ga;
     if (SYM && d == 0.0) d = low ? 0.0 : -0.0;
     const double h2 = fma(d, d, e2 * e2);
-    const double r = h2 * __builtin_amdgcn_rsq(h2);
+    const double r = sqrt_3(h2);
     const double p = r + fabs(d);
-    const double w = (r + r) * p;
-    double u = fabs(e2) * __builtin_amdgcn_rcp(fma(w, __builtin_amdgcn_rsq(w), p));
-    double t = fabs(e2) * __builtin_amdgcn_rcp(p);
+    double u = fabs(e2) * rcp_3(fma(2.0, sqrt_3((0.5 * r) * p), p));  // r p / 2 <= h2: no overflow of its own
+    double t = fabs(e2) * rcp_3(p);
     const double sgn = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, d) ^
                                                       __builtin_bit_cast(unsigned long long, e2));
     u = rot ? __builtin_copysign(u, sgn) : 0.0;
     t = rot ? __builtin_copysign(t, sgn) : 0.0;
-    const double q = fma(u, u, 1.0);
-    double y = __builtin_amdgcn_rcp(q);
-    const double e = fma(-q, y, 1.0);
-    y = fma(y, fma(e, e, e), y);  // 1 / q: the estimate's error cubed
-    const double s = (u + u) * y;
+    const double y = rcp_3(fma(u, u, 1.0)), s = (u + u) * y;
     if constexpr (SYM) {
-        const double c = fma(-u, u, 1.0) * y;
+        const double c = fma(-u, s, 1.0);
 #pragma unroll
         for (int k = 0; k < RPL; ++k) {
             const double a = own[k], b = part[k];
@@ -868,10 +873,12 @@ __device__ __forceinline__ bool jacobi_rotate(double (&own)[RPL], double (&part)
 // one round to the next the second block's columns move between the groups by one DPP lane
 // exchange. Blocks meet by the circle method: lp / 8 - 1 exchanges through LDS, one barrier each,
 // per sweep of lp - 1 rounds. A round is bound by the issue of one wave's instructions (about 8
-// cycles each with one wave per SIMD, 6 with two): 760 cycles at lp = 64, 1650 at lp = 128, where
+// cycles each with one wave per SIMD, 6 with two): 820 cycles at lp = 64, 1750 at lp = 128, where
 // a round through LDS with its own barrier took 1500 and 3300. Per launch, spectra decaying by
-// e^-6 over l: lp = 32, 64, 96, 128 59, 176, 459, 781 us (86, 275, 776, 1390 us before); the
-// factorisation is 28 us of it at lp = 64 and 95 us at lp = 128. Sixteen lanes per pair, and so two
+// e^-6 over l, Gram route: lp = 32, 64, 96, 128 69, 187, 484, 829 us, against 104, 341, 886, 1577 us
+// for rounds through LDS; the factorisation is 28 us of it at lp = 64 and 95 us at lp = 128. The
+// errors of a factor's modes against the exact ones are no larger than there (lp = 16, 32, 64, 128:
+// 1.08, 3.2, 11, 41e-15 rms, there 1.07, 3.4, 12, 42e-15). Sixteen lanes per pair, and so two
 // waves per SIMD at lp = 64, would issue 1.6 x the instructions for 1.3 x the issue rate.
 // LDS holds the blocks as register images: chunk kc of block b at ((b KC + kc) 64 + lane) 16 bytes,
 // so every access is 1 KB contiguous.
