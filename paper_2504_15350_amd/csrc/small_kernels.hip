@@ -863,8 +863,8 @@ __device__ __forceinline__ bool jacobi_rotate(double (&own)[RPL], double (&part)
 // columns are zero, as are their sigma and UB columns).
 // Factorisation: lane i of wave w keeps rows i, i + 64 and columns 16 w .. 16 w + 15 of the
 // Schur complement (original order) in registers. Every wave carries the diagonal and finds the
-// pivot by itself (the largest remaining entry as an FP32 fraction of the largest, lowest index
-// on ties; the next pivot is found while the update runs), the lane holding the pivot row publishes
+// pivot by itself (the largest remaining entry, lowest index on ties, compared by the halves of its
+// bits; the next pivot is found while the update runs), the lane holding the pivot row publishes
 // its part, and one barrier later every wave reads the row as the multipliers (the matrix is
 // symmetric): one barrier per step, no data moved, and the reciprocal root is taken before it.
 // Sweeps: the columns form blocks of eight. A wave holds two blocks in registers, one column of
@@ -937,34 +937,50 @@ __device__ __forceinline__ void jacobi_chol_body(const double* __restrict__ G, i
             asm volatile("" : "+v"(dg[cc]));
             dg[cc] = live ? dg[cc] : 0.0;
         }
-        // the largest diagonal entry, as the scale of the FP32 pivot search
+        // the largest diagonal entry scales the threshold
         double dm = dg[0];
         if constexpr (CPL > 1) dm = fmax(dm, dg[CPL - 1]);
-        dm = wave_max(dm);
-        const double scale = dm > 0.0 ? 1.0 / dm : 0.0;
-        const int thr = __builtin_bit_cast(int, (float)LP * 0x1.0p-53f);
-        // the next pivot: row, and whether one is left that is not negligible (or not finite).
-        // The FP32 fractions are compared by their bits (non-negative, so the orders agree; a
-        // negative or NaN remainder and a finished row lose against thr).
-        auto find = [&](int& pv) {
+        const double thr = (double)LP * 0x1.0p-53 * wave_max(dm);
+        // the next pivot: row and value, and whether one is left that is not negligible (or not finite).
+        // Positive doubles are in the order of their bits: the upper halves decide, the lower ones
+        // between equals (a negative or NaN remainder and a finished row lose against any).
+        auto find = [&](int& pv, double& app) {
             int v[CPL], vm = -1;
 #pragma unroll
             for (int cc = 0; cc < CPL; ++cc) {
-                const double x = dg[cc] * scale;
-                v[cc] = (!done[cc] && x <= 2.0) ? __builtin_bit_cast(int, (float)x) : -1;
+                v[cc] = !done[cc] && dg[cc] > 0.0 ? (int)(__builtin_bit_cast(unsigned long long, dg[cc]) >> 32) : -1;
                 vm = max(vm, v[cc]);
             }
             const int vmax = wave_max(vm);
+            unsigned long long m[CPL];
+            int count = 0;
+#pragma unroll
+            for (int cc = 0; cc < CPL; ++cc) {
+                m[cc] = __ballot(v[cc] == vmax);
+                count += __popcll(m[cc]);
+            }
+            if (count > 1) {  // uniform
+                int w[CPL], wm = INT32_MIN;
+#pragma unroll
+                for (int cc = 0; cc < CPL; ++cc) {
+                    const int lo = (int)((unsigned)__builtin_bit_cast(unsigned long long, dg[cc]) ^ 0x80000000u);
+                    w[cc] = v[cc] == vmax ? lo : INT32_MIN;
+                    wm = max(wm, w[cc]);
+                }
+                const int wmax = wave_max(wm);
+#pragma unroll
+                for (int cc = 0; cc < CPL; ++cc) m[cc] &= __ballot(w[cc] == wmax);
+            }
             pv = 0;
 #pragma unroll
-            for (int cc = CPL - 1; cc >= 0; --cc) {
-                const unsigned long long m = __ballot(v[cc] == vmax);
-                if (m != 0) pv = 64 * cc + __ffsll(m) - 1;
-            }
-            return __builtin_amdgcn_readfirstlane(vmax) > thr;
+            for (int cc = CPL - 1; cc >= 0; --cc)
+                if (m[cc] != 0) pv = 64 * cc + __ffsll(m[cc]) - 1;
+            app = CPL > 1 && pv >= 64 ? read_lane(dg[CPL - 1], pv & 63) : read_lane(dg[0], pv & 63);
+            return __builtin_amdgcn_readfirstlane(vmax) >= 0 && app > thr;
         };
         int rank = l, pv;
-        bool more = find(pv);
+        double app;
+        bool more = find(pv, app);
         __syncthreads();
         for (int j = 0; j < l; ++j) {
             if (!more) {  // the same in every wave
@@ -972,8 +988,6 @@ __device__ __forceinline__ void jacobi_chol_body(const double* __restrict__ G, i
                 break;
             }
             double* pr = buf[j & 1];
-            const int pl = pv & 63;
-            const double app = CPL > 1 && pv >= 64 ? read_lane(dg[CPL - 1], pl) : read_lane(dg[0], pl);
 #pragma unroll
             for (int cc = 0; cc < CPL; ++cc)
                 if (lane + 64 * cc == pv) {
@@ -999,7 +1013,7 @@ __device__ __forceinline__ void jacobi_chol_body(const double* __restrict__ G, i
                 dg[cc] = fma(-lij[cc], lij[cc], dg[cc]);
                 m[cc] = -lij[cc] * inv;
             }
-            more = find(pv);
+            more = find(pv, app);
 #pragma unroll
             for (int cc = 0; cc < CPL; ++cc) fma16_bcast(a[cc], rk, m[cc]);
         }
