@@ -256,6 +256,14 @@ template <bool LO, int NT> struct stq16_grid {
                          WN = NT <= 2 ? 1 : !(LO && NT >= 4) ? 2 : (NT % 4 != 0 && NT % 3 == 0) ? 3 : 4;
 };
 
+// A last step past row m: inside the loop, or after it (AFTER), so that the loop holds neither the branch
+// nor its addresses. After it for hi + lo with 16 waves, whose 128 registers do not hold both (80 columns:
+// 5 spilled, 142 -> 136 us at 100003 x 2000; 120 columns, 1048576 x 10000: 6.29 -> 6.23 ms), and at 48
+// columns (262144 x 3000: 372 -> 350 us); elsewhere inside, where the second copy of the step's work costs
+// more (hi, 1048576 x 10000: 4.69 against 4.75 ms; hi + lo with 32 columns, 30000 x 500: 46.5 against 48.5
+// us; with 96, 8192 x 90225: 391 against 396 us).
+template <bool LO, int NT> constexpr bool stq16_edge_after() { return LO && (stq16_grid<LO, NT>::WN == 4 || NT == 3); }
+
 template <typename T16, int NT, bool LO>
 __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restrict__ S, int64_t ldS, int64_t m,
                                            int64_t n, const GLOBAL unsigned short* __restrict__ Qh,
@@ -263,6 +271,7 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
                                            GLOBAL float* __restrict__ Zp, int64_t nP, int nsplit, int ncb, int tile) {
     constexpr int WM = stq16_grid<LO, NT>::WM, WN = stq16_grid<LO, NT>::WN, NTHR = 64 * WM * WN;
     constexpr int R = STQ16_R, HB = STQ16_HB;
+    constexpr bool AFTER = stq16_edge_after<LO, NT>();
     // column stride of the LDS blocks: 288 bytes. The LDS serves 32 lanes of a 16-byte read per
     // cycle over a 512-byte window (measured on gfx950): lanes (column c, chunk kg < 2) then hit
     // 16-byte slot 18 c + kg mod 32, all distinct; a 272-byte stride (17 c + kg) put two lanes on
@@ -319,57 +328,63 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
         }
     };
     if (ib < m) fetch(ib);
-    for (int64_t i0 = ib; i0 < m; i0 += stride) {
-        __syncthreads();  // previous step fully consumed
-        if (i0 + R > m) {
+    int64_t next = ib;
+#pragma unroll
+    for (int part = AFTER ? 0 : 1; part < 2; ++part) {  // AFTER: the steps inside S, then a last one past row m
+        int64_t i0 = next;
+        for (; part == 0 ? i0 + R <= m : i0 < m; i0 += stride) {
+            __syncthreads();  // previous step fully consumed
+            if (AFTER ? part == 1 : i0 + R > m) {
 #pragma unroll 1
-            for (int ch = tid; ch < SCHT; ch += NTHR) {
-                const int64_t i = i0 + 8 * (ch % LPC), j = j0 + ch / LPC;
-                *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) =
-                    run_fix<unsigned short, 8>(run_load<unsigned short, 8>(S, ldS, m, n, i, j), m, n, i, j);
-            }
-        } else {
+                for (int ch = tid; ch < SCHT; ch += NTHR) {
+                    const int64_t i = i0 + 8 * (ch % LPC), j = j0 + ch / LPC;
+                    *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) =
+                        run_fix<unsigned short, 8>(run_load<unsigned short, 8>(S, ldS, m, n, i, j), m, n, i, j);
+                }
+            } else {
 #pragma unroll
-            for (int q = 0; q < SCH; ++q) {
+                for (int q = 0; q < SCH; ++q) {
+                    const int ch = tid + NTHR * q;
+                    if (SCHT % NTHR == 0 || ch < SCHT)
+                        *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) = sr[q];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < QPT; ++q) {
                 const int ch = tid + NTHR * q;
-                if (SCHT % NTHR == 0 || ch < SCHT)
-                    *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) = sr[q];
-            }
-        }
+                if (ch < QCH) {
 #pragma unroll
-        for (int q = 0; q < QPT; ++q) {
-            const int ch = tid + NTHR * q;
-            if (ch < QCH) {
+                    for (int h = 0; h < NQ; ++h)
+                        *reinterpret_cast<u16x8*>(qs + (h * 16 * NT + ch / LPC) * LDS_ + 8 * (ch % LPC)) = qr[h][q];
+                }
+            }
+            __syncthreads();
+            if (i0 + stride < m) fetch(i0 + stride);  // next step, in flight during this one's work
+#pragma unroll
+            for (int k = 0; k < R / 32; ++k) {
+                u16x8 b[NQ][NTW];
 #pragma unroll
                 for (int h = 0; h < NQ; ++h)
-                    *reinterpret_cast<u16x8*>(qs + (h * 16 * NT + ch / LPC) * LDS_ + 8 * (ch % LPC)) = qr[h][q];
-            }
-        }
-        __syncthreads();
-        if (i0 + stride < m) fetch(i0 + stride);  // next step, in flight during this one's work
 #pragma unroll
-        for (int k = 0; k < R / 32; ++k) {
-            u16x8 b[NQ][NTW];
+                    for (int c = 0; c < NTW; ++c) {
+                        const int nt = NTW * wn + c;
+                        if (NT % WN == 0 || nt < NT)
+                            b[h][c] = *reinterpret_cast<const u16x8*>(qs + (h * 16 * NT + 16 * nt + r16) * LDS_ + 32 * k +
+                                                                      8 * kg);
+                    }
 #pragma unroll
-            for (int h = 0; h < NQ; ++h)
+                for (int t = 0; t < MT; ++t) {
+                    const u16x8 a = *reinterpret_cast<const u16x8*>(ss + (16 * MT * wm + 16 * t + r16) * LDS_ + 32 * k +
+                                                                    8 * kg);
 #pragma unroll
-                for (int c = 0; c < NTW; ++c) {
-                    const int nt = NTW * wn + c;
-                    if (NT % WN == 0 || nt < NT)
-                        b[h][c] = *reinterpret_cast<const u16x8*>(qs + (h * 16 * NT + 16 * nt + r16) * LDS_ + 32 * k +
-                                                                  8 * kg);
+                    for (int h = 0; h < NQ; ++h)  // every accumulator: hi, then lo
+#pragma unroll
+                        for (int c = 0; c < NTW; ++c)
+                            if (NT % WN == 0 || NTW * wn + c < NT) acc[t][c] = mma16<T16>::run(a, b[h][c], acc[t][c]);
                 }
-#pragma unroll
-            for (int t = 0; t < MT; ++t) {
-                const u16x8 a = *reinterpret_cast<const u16x8*>(ss + (16 * MT * wm + 16 * t + r16) * LDS_ + 32 * k +
-                                                                8 * kg);
-#pragma unroll
-                for (int h = 0; h < NQ; ++h)  // every accumulator: hi, then lo
-#pragma unroll
-                    for (int c = 0; c < NTW; ++c)
-                        if (NT % WN == 0 || NTW * wn + c < NT) acc[t][c] = mma16<T16>::run(a, b[h][c], acc[t][c]);
             }
         }
+        if (AFTER) next = i0;
     }
     GLOBAL float* zp = Zp + (int64_t)sp * nP * (16 * NT);  // FP32 slabs (summed in FP64 afterwards)
 #pragma unroll
