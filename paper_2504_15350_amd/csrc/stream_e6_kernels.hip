@@ -78,8 +78,11 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
     // Unguarded vector loads, a uniform base per column plus a 32-bit lane offset. A wave with rows past
     // m takes whole runs too (rows of the column's padding or of the next column, which meet only
     // output rows past m, written as zero), except where the last column of S is in the step, whose
-    // runs could leave S, or a column is shorter than a tile.
-    const bool inside = iw + 16 * U <= m, fast = (inside || ldS >= 256) && row_offset_fits(ldS);
+    // runs could leave S, or a column is shorter than a tile. Where ldS is too large for 32-bit offsets,
+    // 64-bit addresses at 16 columns, and the guarded loads of the edges at more, whose matrix-core work
+    // hides their selects (34000000 x 80: 16 columns 2780 -> 2660 us, 60 columns 5060 with either).
+    const bool narrow = row_offset_fits(ldS), inside = iw + 16 * U <= m;
+    const bool fast = (inside || ldS >= 256) && (narrow || NT == 1);
     auto plain = [&](int64_t j0) { return fast && j0 + 32 <= (inside ? n : n - 1); };
     const uint32_t so = row_offset(g, ldS, irow);
     f32x4 acc[U][NT];
@@ -89,11 +92,16 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
         for (int c = 0; c < NT; ++c) acc[t][c] = f32x4{0, 0, 0, 0};
     Vec sv[8];
     auto load_s = [&](int64_t j0) {
-        if (plain(j0)) {
+        if (plain(j0) && (NT > 1 || narrow)) {
             const GLOBAL char* p = reinterpret_cast<const GLOBAL char*>(S + j0 * ldS);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 sv[i] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL run_vec_u<float, U>*>(p + 4 * i * ldS + so));
+        } else if (NT == 1 && plain(j0)) {
+            const GLOBAL float* p = S + (j0 + 8 * g) * ldS + irow;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                sv[i] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL run_vec_u<float, U>*>(p + i * ldS));
         } else if (m >= U) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) sv[i] = run_load<float, U, true>(S, ldS, m, n, irow, j0 + 8 * g + i);
@@ -175,7 +183,7 @@ __device__ __forceinline__ void sx_e6_body(const GLOBAL float* S, int64_t ldS, i
         }
     }
     if constexpr (EN) *ssq = sq;
-    // D[4 g + v][r] of tile t: row iw + 4 (4 g + v) + t, output column 16 c + r
+    // D[4 g + v][r] of tile t: row iw + U (4 g + v) + t, output column 16 c + r
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
         if (16 * c + r16 >= cmax) continue;
