@@ -380,7 +380,8 @@ template <int NB>
 __device__ __forceinline__ void chol_body(const GramArgs& a, const CholShared& sh) {
     constexpr int LP = 16 * NB, PW = (NB + 3) / 4;  // PW: panel waves
     double *Rs = sh.R, *Xs = sh.X, *gd = sh.gd;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // branches on it are scalar: no masks to keep
     const int n = lane & 15, kg = lane >> 4;  // MFMA lane; kg is also the lane's row of 16 lanes
     const CholArgs& c = a.chol;
     const int l = c.l, mode = c.mode;
@@ -392,11 +393,14 @@ __device__ __forceinline__ void chol_body(const GramArgs& a, const CholShared& s
     f64x4 w[NB];  // A[16 i + kg + 4 v][16 wave + n], then X
     bool fin = true;
     auto load = [&](bool first, double shift) {
+        // formed anew by the second call: kept from the first, its masks and addresses spill
+        int ln = n, ll = l;
+        asm volatile("" : "+v"(ln), "+s"(ll));
 #pragma unroll
         for (int i = 0; i < NB; ++i)
             if (wave < NB && i <= wave) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) w[i][v] = G[(16 * i + kg + 4 * v) * LP + 16 * wave + n];
+                for (int v = 0; v < 4; ++v) w[i][v] = G[(16 * i + kg + 4 * v) * LP + 16 * wave + ln];
             }
 #pragma unroll
         for (int i = 0; i < NB; ++i)
@@ -406,16 +410,16 @@ __device__ __forceinline__ void chol_body(const GramArgs& a, const CholShared& s
                 if (i == wave) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (kg + 4 * v == n) {
-                            if (first) gd[16 * wave + n] = w[i][v];
+                        if (kg + 4 * v == ln) {
+                            if (first) gd[16 * wave + ln] = w[i][v];
                             w[i][v] += shift;
                         }
                 }
-                if (16 * wave + 16 > l) {  // padding (i <= wave: its rows are in the same block column)
+                if (16 * wave + 16 > ll) {  // padding (i <= wave: its rows are in the same block column)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int row = 16 * i + kg + 4 * v, col = 16 * wave + n;
-                        if (row >= l || col >= l) w[i][v] = row == col ? 1.0 : 0.0;
+                        const int row = 16 * i + kg + 4 * v, col = 16 * wave + ln;
+                        if (row >= ll || col >= ll) w[i][v] = row == col ? 1.0 : 0.0;
                     }
                 }
             }
