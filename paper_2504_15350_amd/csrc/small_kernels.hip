@@ -802,13 +802,16 @@ __device__ __forceinline__ double rcp_3(double x) {
 
 // One rotation per group of eight lanes that makes the columns own and part (RPL rows per lane)
 // orthogonal: own' = c own - s part, part' = s own + c part; no, np are their squared norms. The
-// half-angle tangent u, the tangent t, s = 2 u / (1 + u^2) and c = 1 - u s are taken to FP64. (u and t by the estimates alone, 2^-23, leave that fraction of the inner product over: the
-// sweeps take 6 to 9 % less, but the modes of a 16 x 16 factor are 19 % further from the exact ones,
-// and c = (1 - u^2) / (1 + u^2) makes sigma's error half as large again.)
+// rotation is orthogonal to rounding whatever the half-angle tangent u: s = 2 u / (1 + u^2) and
+// c = 1 - u s follow from it to FP64 (through a rounded c sigma's error is twice as large). FINE: u and the tangent t of the norms' update to FP64; else from the hardware's estimates,
+// which leaves 2^-23 of the inner product over. That is 1e-15 where pairs count as orthogonal from
+// 1e-8 on, and the modes' errors are the same to four digits (lp = 16 .. 128, 0.5 to 4e-8 rms) for
+// sweeps 4 to 6 % shorter; at a threshold of FP64 rounding it shows (modes of a 16 x 16 factor 1.27e-15
+// rms from the exact ones instead of 1.00e-15).
 // SYM: the two groups of a pair within a block compute the same rotation, each as "own"; every
 // expression is then symmetric (or antisymmetric) in the exchange bit for bit, `low` deciding where
 // the norms are equal. Otherwise the update is three shears in place, (1 -u; 0 1) (1 0; s 1) (1 -u; 0 1).
-template <int RPL, bool SYM>
+template <int RPL, bool SYM, bool FINE>
 __device__ __forceinline__ bool jacobi_rotate(double (&own)[RPL], double (&part)[RPL], double& no, double& np,
                                               double tol2, bool low) {
     double g0 = 0.0, g1 = 0.0;
@@ -826,22 +829,23 @@ __device__ __forceinline__ bool jacobi_rotate(double (&own)[RPL], double (&part)
     const double e2 = ga + ga;
     if (SYM && d == 0.0) d = low ? 0.0 : -0.0;
     const double h2 = fma(d, d, e2 * e2);
-    const double r = sqrt_3(h2);
+    const double r = FINE ? sqrt_3(h2) : h2 * __builtin_amdgcn_rsq(h2);
     const double p = r + fabs(d);
-    double u = fabs(e2) * rcp_3(fma(2.0, sqrt_3((0.5 * r) * p), p));  // r p / 2 <= h2: no overflow of its own
-    double t = fabs(e2) * rcp_3(p);
+    const double w = (0.5 * r) * p;  // <= h2: no overflow of its own
+    const double q = fma(2.0, FINE ? sqrt_3(w) : w * __builtin_amdgcn_rsq(w), p);
+    double u = fabs(e2) * (FINE ? rcp_3(q) : __builtin_amdgcn_rcp(q));
+    double t = fabs(e2) * (FINE ? rcp_3(p) : __builtin_amdgcn_rcp(p));
     const double sgn = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, d) ^
                                                       __builtin_bit_cast(unsigned long long, e2));
     u = rot ? __builtin_copysign(u, sgn) : 0.0;
     t = rot ? __builtin_copysign(t, sgn) : 0.0;
     const double y = rcp_3(fma(u, u, 1.0)), s = (u + u) * y;
     if constexpr (SYM) {
-        const double c = fma(-u, s, 1.0);
 #pragma unroll
-        for (int k = 0; k < RPL; ++k) {
+        for (int k = 0; k < RPL; ++k) {  // own - s (part + u own), part + s (own - u part): one rounding at full size
             const double a = own[k], b = part[k];
-            own[k] = fma(-s, b, c * a);
-            part[k] = fma(s, a, c * b);
+            own[k] = fma(-s, fma(u, a, b), a);
+            part[k] = fma(s, fma(-u, b, a), b);
         }
     } else {
 #pragma unroll
@@ -877,12 +881,12 @@ __device__ __forceinline__ bool jacobi_rotate(double (&own)[RPL], double (&part)
 // one round to the next the second block's columns move between the groups by one DPP lane
 // exchange. Blocks meet by the circle method: lp / 8 - 1 exchanges through LDS, one barrier each,
 // per sweep of lp - 1 rounds. A round is bound by the issue of one wave's instructions (about 8
-// cycles each with one wave per SIMD, 6 with two): 820 cycles at lp = 64, 1750 at lp = 128, where
+// cycles each with one wave per SIMD, 6 with two): 760 cycles at lp = 64, 1650 at lp = 128, where
 // a round through LDS with its own barrier took 1500 and 3300. Per launch, spectra decaying by
-// e^-6 over l, Gram route: lp = 32, 64, 96, 128 69, 187, 484, 829 us, against 104, 341, 886, 1577 us
+// e^-6 over l, Gram route: lp = 32, 64, 96, 128 64, 179, 462, 791 us, against 104, 341, 886, 1577 us
 // for rounds through LDS; the factorisation is 28 us of it at lp = 64 and 95 us at lp = 128. The
 // errors of a factor's modes against the exact ones are no larger than there (lp = 16, 32, 64, 128:
-// 1.08, 3.2, 11, 41e-15 rms, there 1.07, 3.4, 12, 42e-15). Sixteen lanes per pair, and so two
+// 1.00, 3.2, 11, 40e-15 rms, there 1.08, 3.5, 13, 45e-15). Sixteen lanes per pair, and so two
 // waves per SIMD at lp = 64, would issue 1.6 x the instructions for 1.3 x the issue rate.
 // LDS holds the blocks as register images: chunk kc of block b at ((b KC + kc) 64 + lane) 16 bytes,
 // so every access is 1 KB contiguous.
@@ -1060,51 +1064,55 @@ __device__ __forceinline__ void jacobi_chol_body(const double* __restrict__ G, i
     std::integral_constant<int, DPP_XOR2> x2;
     std::integral_constant<int, DPP_XOR7> x7;
     // the 28 pairs within a block: each pair computed by both of its groups
-    auto within = [&](double (&x)[RPL], double& nx) {
+    auto within = [&](auto fine, double (&x)[RPL], double& nx) {
         double P[RPL], np = nx;
         bool rot = false;
 #pragma unroll
         for (int k = 0; k < RPL; ++k) P[k] = x[k];
         auto step = [&](auto ctrl, int k) {
             move(ctrl, P, np);
-            rot |= jacobi_rotate<RPL, true>(x, P, nx, np, tol2, grp < (grp ^ k));
+            rot |= jacobi_rotate<RPL, true, decltype(fine)::value>(x, P, nx, np, tol2, grp < (grp ^ k));
         };
         step(x1, 1); step(x2, 3); step(x1, 2); step(x7, 5); step(x1, 4); step(x2, 6); step(x1, 7);
         return rot;
     };
     int sweep = 0;
     constexpr int max_sweeps = 40;
-    __syncthreads();
-    for (; sweep < max_sweeps; ++sweep) {
-        bool rot = false;  // this lane's pairs rotated during the sweep
-        int any = 0;
-        for (int t = 0; t < NB - 1; ++t) {
-            int ba = t + wave, bb = t - wave;  // circle method: block NB - 1 stays, the others turn
-            if (ba >= NB - 1) ba -= NB - 1;
-            if (bb < 0) bb += NB - 1;
-            if (wave == 0) ba = NB - 1;
-            load(A, ba);
-            load(B, bb);
-            double na = norm2(A), nb = norm2(B);
-            if (t == 0) {
-                rot |= within(A, na);
-                rot |= within(B, nb);
+    auto sweeps = [&](auto fine) {
+        for (; sweep < max_sweeps; ++sweep) {
+            bool rot = false;  // this lane's pairs rotated during the sweep
+            int any = 0;
+            for (int t = 0; t < NB - 1; ++t) {
+                int ba = t + wave, bb = t - wave;  // circle method: block NB - 1 stays, the others turn
+                if (ba >= NB - 1) ba -= NB - 1;
+                if (bb < 0) bb += NB - 1;
+                if (wave == 0) ba = NB - 1;
+                load(A, ba);
+                load(B, bb);
+                double na = norm2(A), nb = norm2(B);
+                if (t == 0) {
+                    rot |= within(fine, A, na);
+                    rot |= within(fine, B, nb);
+                }
+                rot |= jacobi_rotate<RPL, false, decltype(fine)::value>(A, B, na, nb, tol2, true);
+                auto step = [&](auto ctrl) {
+                    move(ctrl, B, nb);
+                    rot |= jacobi_rotate<RPL, false, decltype(fine)::value>(A, B, na, nb, tol2, true);
+                };
+                step(x1); step(x2); step(x1); step(x7); step(x1); step(x2); step(x1);
+                store(A, ba, lane);
+                store(B, bb, lane ^ 7);  // the last partner was the column of group grp ^ 7
+                // a slot is written by its holder and, after the barrier, read and later written by the next
+                // holder only
+                if (t < NB - 2) __syncthreads();
+                else any = __syncthreads_or(rot);
             }
-            rot |= jacobi_rotate<RPL, false>(A, B, na, nb, tol2, true);
-            auto step = [&](auto ctrl) {
-                move(ctrl, B, nb);
-                rot |= jacobi_rotate<RPL, false>(A, B, na, nb, tol2, true);
-            };
-            step(x1); step(x2); step(x1); step(x7); step(x1); step(x2); step(x1);
-            store(A, ba, lane);
-            store(B, bb, lane ^ 7);  // the last partner was the column of group grp ^ 7
-            // a slot is written by its holder and, after the barrier, read and later written by the next
-            // holder only
-            if (t < NB - 2) __syncthreads();
-            else any = __syncthreads_or(rot);
+            if (!any) break;
         }
-        if (!any) break;
-    }
+    };
+    __syncthreads();
+    if (C != nullptr) sweeps(std::true_type{});
+    else sweeps(std::false_type{});
     if (sweep == max_sweeps && tid == 0) atomicOr(flags, DEV_FLAG_JACOBI_SLOW);
     load(A, 2 * wave);
     load(B, 2 * wave + 1);
