@@ -1,7 +1,9 @@
 """What the host records for the kernels, checked without a GPU: rpod_abi.cpp and
 warm_abi.cpp compiled host-only with AddressSanitizer and UndefinedBehaviorSanitizer
-against the stand-ins of tests/host_records/checks.cpp: the bounds of the FP32
-passes' 32-bit offsets."""
+against the stand-ins of tests/host_records/checks.cpp. The grid of every Gram
+reduction and the record of the factorisation it ends in, the bounds of the FP32
+passes' 32-bit offsets, and every part of an adaptive plan's program: a stop after
+the first, a middle and the last block runs exactly one finish."""
 
 import os
 import shutil
