@@ -114,7 +114,8 @@ def make_input(w, dev):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("stream_kernels.hip", "stream16_kernels.hip", "stream_e6_kernels.hip", "split_ops.hpp", "device_common.hpp"):
+    for f in ("stream_kernels.hip", "stream16_kernels.hip", "stream_e6_kernels.hip", "split_ops.hpp", "offsets.hpp",
+              "device_common.hpp"):
         with open(os.path.join(ROOT, "paper_2504_15350_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

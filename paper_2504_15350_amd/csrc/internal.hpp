@@ -57,7 +57,7 @@ int stq32_block_cols();
 // product added when lo is set, written as FP32 slabs (the FP32
 // accumulators). Splits are interleaved in steps of
 // stq16_rows_per_step(lo) rows; tiles: ncb = nP / stq16_block_cols(lo) x
-// nsplit. vec: S 16-byte aligned with ldS a multiple of 8.
+// nsplit. S at any 2-byte alignment (vec is not used).
 hipError_t launch_sx16(int tin, int nt, bool vec, const GroupLaunch<SxArgs>& L, hipStream_t st);
 hipError_t launch_stq16(int tin, int nt, bool lo, bool vec, const GroupLaunch<StqArgs>& L, hipStream_t st);
 int stq16_block_cols(bool lo);

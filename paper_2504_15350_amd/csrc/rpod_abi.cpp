@@ -440,7 +440,7 @@ struct Recorder {
         s.tin = L0().tin; s.tout = L0().tacc; s.nt = first ? L0().nta : L0().nt; s.pass = 0;
         s.vec = true;
         for (const Item* it : C) {
-            s.vec = s.vec && (it->d.ld % (s16 ? 8 : 4) == 0);
+            s.vec = s.vec && (s16 || f32 || it->d.ld % 4 == 0);  // FP64: 16-byte loads (the others take any alignment)
             const double sz = (double)dt_size(it->L.tin);
             s.bytes += (double)it->d.m * it->d.n * sz + (double)it->d.n * it->L.l * sz + (double)it->d.m * it->L.l * 4.0;
             s.flops += 2.0 * it->d.m * it->d.n * it->L.l;
@@ -491,8 +491,8 @@ struct Recorder {
         s.vec = true;
         bool wide = false;  // FP32: operands too tall for the 32-bit offsets of the steps for columns off the lines
         for (const Item* it : C) {
-            // FP32: columns on 128-byte lines pick the step shape; otherwise 16-byte loads
-            s.vec = s.vec && (it->d.ld % (s16 ? 8 : f32 ? 32 : 4) == 0);
+            // FP32: columns on 128-byte lines pick the step shape; FP64: 16-byte loads; 16-bit: any alignment
+            s.vec = s.vec && (s16 || it->d.ld % (f32 ? 32 : 4) == 0);
             wide = wide || (f32 && !chunk_offset_fits(std::max(it->d.ld, it->L.mP)));
             const double sz = (double)dt_size(it->L.tin);
             s.bytes += (double)it->d.m * it->d.n * sz + (double)it->d.n * it->L.l * sz + (double)it->d.m * it->L.l * 4.0;
@@ -1998,9 +1998,8 @@ rpod_status rpod_energy(rpod_plan plan, int32_t item, double delta, double* ener
     return RPOD_OK;
 }
 
-// scratch of rpod_reconstruct: abar, the two sums, the error's partial sums,
-// and for FP32 fields on the matrix cores the augmented modes, one chunk's
-// operand and its launch record
+// scratch of rpod_reconstruct: the time-averaged coefficients, the error's two sums with the count of
+// finished tiles, its partial sums per tile, and for FP32 fields the coefficients split into BF16 parts
 struct ReconLayout {
     size_t abar, out2, part, op, op_bytes, total;
 };

@@ -25,8 +25,8 @@
 namespace rpod {
 
 // A 16-byte load at any 4-byte alignment: gfx950 global loads need no more, so odd leading
-// dimensions of S take the same path as padded ones (100003 x 2000, ld 100003, 60 columns: S X 188 us,
-// against 283 with four scalar loads).
+// dimensions of S take the same path as padded ones (100003 x 2000, ld 100003, 60 columns: S X 184 us,
+// against 283 with four scalar loads). Times of passes in this file are those inside a call.
 typedef float e6_f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // ---------------------------------------------------------------------------
@@ -43,8 +43,8 @@ typedef float e6_f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 // Waves: four of four tiles, whose operand reads from LDS serve four products
 // each; at 128 columns these take more than half of the register file and leave
 // one wave per SIMD, and eight of two tiles are the faster (262144 x 1000: 376
-// against 484 us, 65536 x 3000: 272 against 358; 1048576 x 128 times 128 x 128:
-// 338 against 387; at 112 columns, where two waves still fit, 581 against 459 at
+// against 484 us, 65536 x 3000: 270 against 358; 1048576 x 128 times 128 x 128:
+// 338 against 387; at 112 columns, where two waves still fit, 625 against 466 at
 // 131072 x 3500). Every entry has the same order of sums in either.
 // ---------------------------------------------------------------------------
 constexpr int E6_XLD = 40;  // halfwords per staged X column (32 rows + pad)
@@ -53,10 +53,10 @@ constexpr int sx_waves(int nt, bool en) { return nt == 8 && !en ? 8 : 4; }
 // EARLY: the next step's S columns are loaded as soon as the current ones are split, before the
 // matrix-core work; else after it. Early in products with few columns of S (the tall R^-1 applications,
 // the lift: with four steps per workgroup every exposed load latency counts), with one workgroup per CU
-// or less, which has no other to hide the loads (20000 x 1000, 60 columns: 65 against 75 us; 5003 x 701:
-// 45 against 51), at 16 columns (131072 x 2000: 164 against 173) and at 128 (65536 x 3000 with four waves:
-// 304 against 349 us); else late (262144 x 5000, 60 columns: 1043 against 1052 us; 100003 x 2000: 194
-// against 200; 131072 x 3500, 110 columns: 459 against 486).
+// or less, which has no other to hide the loads (20000 x 1000, 60 columns: 66 against 75 us; 5003 x 701:
+// 45 against 51), at 16 columns (131072 x 2000: 165 against 173) and at 128 (65536 x 3000: 270 against 303
+// us; 262144 x 1000: 374 against 418); else late (262144 x 5000, 60 columns: 958 against 968 us; 100003 x
+// 2000: 184 against 195; 131072 x 3500, 110 columns: 470 against 509).
 constexpr int64_t SX_FEW_TILES = 256;
 constexpr bool sx_early_always(int nt) { return nt == 1 || nt == 8; }
 
@@ -266,10 +266,11 @@ constexpr int E6_R = 32, E6_LDS = E6_R, E6_LDQ = E6_R, E6_HB = 256;
 
 // Waves per workgroup: four of four column tiles while two of them fit a SIMD's registers (two workgroups
 // per CU); at 112 and 128 columns of Q they do not, and eight of two tiles hide more of the loads and
-// splits than one such wave (65536 x 3000, 128 columns: 335 -> 300 us; 131072 x 3500, 110 columns: 660 ->
-// 597; but at 80 columns 40000 x 4000 204 against 178 us, at 60 262144 x 5000 1170 against 1108). Two LDS
-// buffers and one barrier per step measured no better (349 against 363 us at 262144 x 1000 with 128
-// columns, 612 against 590 with 110, 1242 against 1108 at 262144 x 5000 with 60).
+// splits than one such wave (65536 x 3000, 128 columns: 332 -> 303 us; 131072 x 3500, 110 columns: 688 ->
+// 604; but at 80 columns 40000 x 4000 194 against 174 us, at 60 262144 x 5000 1372 against 1071). Two LDS
+// buffers and one barrier per step measured no better on the whole (back to back: 349 against 363 us at
+// 262144 x 1000 with 128 columns, but 612 against 590 with 110 and 1242 against 1108 at 262144 x 5000
+// with 60).
 constexpr int stq_waves(int nt, bool lines) { return lines && nt >= 7 ? 8 : 4; }
 
 template <int NT, int W>
@@ -431,9 +432,9 @@ __device__ __forceinline__ void stq_e6_body(const GLOBAL float* __restrict__ S, 
 // so the workgroup takes its units of 64 rows in two steps of 128 columns x 64
 // rows (runs of 256 bytes, three lines instead of four). The accumulation
 // order of every entry is the one above. 100003 x 2000, 60 columns, ld 100003 /
-// 100008: 293 / 268 -> 240 / 232 us; with columns on lines the steps above are
-// the faster (131072 x 2000: 240 against 264 us), because here a staged Q
-// operand serves two column tiles instead of four. S or Q of 2^26 rows and more
+// 100008: 293 / 268 -> 234 / 223 us; with columns on lines the steps above are
+// the faster (131072 x 2000: by 9 %), because here a staged Q operand serves two
+// column tiles instead of four. S or Q of 2^26 rows and more
 // stays with the steps above: a thread's columns here lie within a 32-bit offset
 // of a uniform base, which in 64 bits takes registers that 96 columns do not have.
 // The S block (128 x 64, FP32) of a step and once per unit the parts of the Q
