@@ -6,7 +6,8 @@
 
 namespace rpod {
 
-// S^T Q: column c < 16 of a block of FP32 columns ld apart, 16-byte chunk k < 16 of the column
+// S^T Q: column c < 16 of a block of FP32 columns ld apart, 16-byte chunk k < 16 of a unit of rows; with
+// k = 0 and 4 i added, row i < ld
 constexpr uint32_t chunk_offset(int c, int64_t ld, int k) { return (uint32_t)c * (uint32_t)(4 * ld) + 16u * (uint32_t)k; }
 constexpr bool chunk_offset_fits(int64_t ld) { return ld < ((int64_t)1 << 26); }
 

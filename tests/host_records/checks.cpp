@@ -121,8 +121,10 @@ static void run(const rpod_desc* d, int count) {
 static void offsets() {
     for (int64_t ld : {(int64_t)1, (int64_t)100003, (int64_t)33554431, (int64_t)33554432, (int64_t)67108863,
                        (int64_t)67108864, (int64_t)71582720, (int64_t)71582976, (int64_t)400000000}) {
-        for (int c = 0; c < 16 && rpod::chunk_offset_fits(ld); ++c)
+        for (int c = 0; c < 16 && rpod::chunk_offset_fits(ld); ++c) {
             for (int k = 0; k < 16; ++k) EXPECT((int64_t)rpod::chunk_offset(c, ld, k) == 4 * ld * c + 16 * k);
+            EXPECT((int64_t)(rpod::chunk_offset(c, ld, 0) + 4 * (uint32_t)(ld - 1)) == 4 * ld * c + 4 * (ld - 1));
+        }
         for (int g = 0; g < 4 && rpod::row_offset_fits(ld); ++g)
             for (int64_t i : {(int64_t)0, ld / 2, ld + 255})
                 EXPECT((int64_t)rpod::row_offset(g, ld, i) == 32 * ld * g + 4 * i);
