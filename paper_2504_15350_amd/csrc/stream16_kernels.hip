@@ -58,6 +58,15 @@ typedef unsigned short u16x8u __attribute__((ext_vector_type(8), aligned(2)));
 __device__ __forceinline__ u16x8 load8(const GLOBAL unsigned short* p) {
     return __builtin_nontemporal_load(reinterpret_cast<const GLOBAL u16x8u*>(p));  // streamed once
 }
+// The rows of a run from row d on, zero after its last
+__device__ __forceinline__ u16x8 shift_rows(u16x8 v, int64_t d) {
+    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+    const u64x2 x = __builtin_bit_cast(u64x2, v);
+    const unsigned long long a = d >= 8 ? 0 : d >= 4 ? x[1] : x[0], b = d >= 4 ? 0 : x[1];
+    const int sh = 16 * ((int)d & 3);
+    return __builtin_bit_cast(u16x8, u64x2{a >> sh | b << 1 << (63 - sh), b >> sh});
+}
+
 // ---------------------------------------------------------------------------
 // Y = S X, 16-bit S and X, FP32 Y. Workgroup: 256 rows, columns in chunks of
 // 32 (one MFMA K). Each chunk of S is staged in LDS column-major (every
@@ -237,12 +246,10 @@ __global__ __launch_bounds__(256, 2) void k_sx16(Group<SxArgs> g) {
 // so every accumulator sees its k steps in row order, hi before lo. Splits
 // are interleaved (step t of split s covers rows 128 (t nsplit + s) .. +127),
 // so the workgroups of one column block read neighbouring pieces of every
-// column. A last step past row m is loaded when it is staged (one step of one
-// split; rows past m must count as zero against any padding of S); a column
-// block past column n reads column n - 1 again there and writes zeros. Measured at 1048576 x 10000, lp = 128 (BF16, back to back): hi
-// 4.71 ms against 5.15 ms for two 4-wave workgroups per CU on 128 x 128
-// blocks (bit-identical slabs), hi + lo 6.27 ms against 7.41 ms (64-row steps
-// there).
+// column. A column block past column n reads column n - 1 again there and writes
+// zeros. Measured at 1048576 x 10000, lp = 128 (BF16, back to back): hi 4.71 ms
+// against 5.15 ms for two 4-wave workgroups per CU on 128 x 128 blocks
+// (bit-identical slabs), hi + lo 6.27 ms against 7.41 ms (64-row steps there).
 // ---------------------------------------------------------------------------
 constexpr int STQ16_HB = 256;  // columns per block
 constexpr int STQ16_R = 128;   // rows per step
@@ -256,13 +263,22 @@ template <bool LO, int NT> struct stq16_grid {
                          WN = NT <= 2 ? 1 : !(LO && NT >= 4) ? 2 : (NT % 4 != 0 && NT % 3 == 0) ? 3 : 4;
 };
 
-// A last step past row m: inside the loop, or after it (AFTER), so that the loop holds neither the branch
-// nor its addresses. After it for hi + lo with 16 waves, whose 128 registers do not hold both (80 columns:
-// 5 spilled, 142 -> 136 us at 100003 x 2000; 120 columns, 1048576 x 10000: 6.29 -> 6.23 ms), and at 48
-// columns (262144 x 3000: 372 -> 350 us); elsewhere inside, where the second copy of the step's work costs
-// more (hi, 1048576 x 10000: 4.69 against 4.75 ms; hi + lo with 32 columns, 30000 x 500: 46.5 against 48.5
-// us; with 96, 8192 x 90225: 391 against 396 us).
-template <bool LO, int NT> constexpr bool stq16_edge_after() { return LO && (stq16_grid<LO, NT>::WN == 4 || NT == 3); }
+// A last step past row m (one step of one split; rows past m must count as zero against any padding of S):
+// its runs are loaded ahead like any other step's, moved inside the column, and shifted back when they are
+// staged, inside the loop or (the branch out of the loop, the step's work written out twice) after it. At 48
+// and 128 columns of hi + lo, where the moved runs' addresses would spill or cost the loop, they are loaded
+// when they are staged, after it. Times at 1000 x 20000 / 5000 x 701 / 262144 x 3000, us:
+//   hi, 12 columns: after 24.9 / 31.7 / 270, inside 24.9 / 33.8 / 291, loaded when staged 33.1 / 38.5 / 267
+//   hi, 112 columns: after 36.8 / 54.6 / 380, inside 36.7 / 55.1 / 381, loaded when staged 41.7 / 60.3 / 390
+//   hi + lo, 60 columns: after 28.2 / 39.5 / 352, inside 28.5 / 40.0 / 361
+//   hi + lo, 75 columns: after 37.8 / 55.8 / 399 (spills), inside 35.0 / 52.8 / 395
+//   hi + lo, 45 columns: loaded when staged 37.2 / 51.2 / 350, after 34.8 / 51.0 / 365, inside 35.3 / 51.0 / 371
+//   hi + lo, 120 columns: loaded when staged 42.8 / 63.1 / 461, after 45.4 / 71.0 / 511 (spills), inside
+//   40.7 / 61.5 / 459; 1048576 x 10000: 6.23, 6.75 and 6.28 ms
+enum class Edge { after, inside, staged };
+template <bool LO, int NT> constexpr Edge stq16_edge() {
+    return LO && (NT == 3 || NT == 8) ? Edge::staged : LO && NT >= 5 ? Edge::inside : Edge::after;
+}
 
 template <typename T16, int NT, bool LO>
 __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restrict__ S, int64_t ldS, int64_t m,
@@ -271,7 +287,8 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
                                            GLOBAL float* __restrict__ Zp, int64_t nP, int nsplit, int ncb, int tile) {
     constexpr int WM = stq16_grid<LO, NT>::WM, WN = stq16_grid<LO, NT>::WN, NTHR = 64 * WM * WN;
     constexpr int R = STQ16_R, HB = STQ16_HB;
-    constexpr bool AFTER = stq16_edge_after<LO, NT>();
+    constexpr Edge EDGE = stq16_edge<LO, NT>();
+    constexpr bool AFTER = EDGE != Edge::inside;
     // column stride of the LDS blocks: 288 bytes. The LDS serves 32 lanes of a 16-byte read per
     // cycle over a 512-byte window (measured on gfx950): lanes (column c, chunk kg < 2) then hit
     // 16-byte slot 18 c + kg mod 32, all distinct; a 272-byte stride (17 c + kg) put two lanes on
@@ -313,8 +330,10 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
                 if (LO) qr[NQ - 1][q] = *reinterpret_cast<const GLOBAL u16x8*>(Ql + off);
             }
         }
-        if (i0 + R > m) return;  // loaded when it is staged
-        const GLOBAL unsigned short* p = S + (j0 + tid / LPC) * ldS + i0 + 8 * (tid % LPC);
+        const bool edge = i0 + R > m;
+        if (edge && (EDGE == Edge::staged || m < 8)) return;  // loaded when it is staged
+        const int64_t row = edge ? min(i0 + 8 * (tid % LPC), m - 8) : i0 + 8 * (tid % LPC);
+        const GLOBAL unsigned short* p = S + (j0 + tid / LPC) * ldS + row;
         if (j0 + HB <= n) {      // whole block inside S: no per-lane bounds
 #pragma unroll
             for (int q = 0; q < SCH; ++q)
@@ -323,7 +342,7 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
 #pragma unroll
             for (int q = 0; q < SCH; ++q) {
                 const int jl = min(tid / LPC + q * CSTEP, (int)(n - 1 - j0));
-                if (SCHT % NTHR == 0 || tid + NTHR * q < SCHT) sr[q] = load8(S + (j0 + jl) * ldS + i0 + 8 * (tid % LPC));
+                if (SCHT % NTHR == 0 || tid + NTHR * q < SCHT) sr[q] = load8(S + (j0 + jl) * ldS + row);
             }
         }
     };
@@ -335,11 +354,25 @@ __device__ __forceinline__ void stq16_body(const GLOBAL unsigned short* __restri
         for (; part == 0 ? i0 + R <= m : i0 < m; i0 += stride) {
             __syncthreads();  // previous step fully consumed
             if (AFTER ? part == 1 : i0 + R > m) {
+                if (EDGE == Edge::staged) {
 #pragma unroll 1
-                for (int ch = tid; ch < SCHT; ch += NTHR) {
-                    const int64_t i = i0 + 8 * (ch % LPC), j = j0 + ch / LPC;
-                    *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) =
-                        run_fix<unsigned short, 8>(run_load<unsigned short, 8>(S, ldS, m, n, i, j), m, n, i, j);
+                    for (int ch = tid; ch < SCHT; ch += NTHR) {
+                        const int64_t i = i0 + 8 * (ch % LPC), j = j0 + ch / LPC;
+                        *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) =
+                            run_fix<unsigned short, 8>(run_load<unsigned short, 8>(S, ldS, m, n, i, j), m, n, i, j);
+                    }
+                } else if (m >= 8) {
+                    const int64_t i = i0 + 8 * (tid % LPC), d = i - min(i, m - 8);  // rows to shift by
+#pragma unroll
+                    for (int q = 0; q < SCH; ++q) {
+                        const int ch = tid + NTHR * q;
+                        if (SCHT % NTHR == 0 || ch < SCHT)
+                            *reinterpret_cast<u16x8*>(ss + (ch / LPC) * LDS_ + 8 * (ch % LPC)) = shift_rows(sr[q], d);
+                    }
+                } else {  // fewer rows than a run
+#pragma unroll 1
+                    for (int e = tid; e < HB * R; e += NTHR)
+                        ss[e / R * LDS_ + e % R] = e % R < m && j0 + e / R < n ? S[(j0 + e / R) * ldS + e % R] : 0;
                 }
             } else {
 #pragma unroll
